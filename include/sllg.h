@@ -141,8 +141,9 @@ sllg_status sllg_build_fcc_sphere(double a_nm, double radius_nm, int64_t *n, int
  * uniform materials, scalar exchange, no cubic anisotropy or demagnetising
  * field; in FP64 only lattices whose sites all have the simple-cubic or bcc
  * links (sllg_get_option "lattice" = 2 when the structure qualifies,
- * "fused_active" = 1 when the next integration takes it); other systems run
- * the two-launch step.  The exchange sum of a site is then added in a fixed
+ * "fused_active" = 1 when the next integration takes it); smaller lattices
+ * of those links run the brick step (one launch per Heun step over bricks of
+ * cells, "brick_active" = 1), other systems the two-launch step.  The exchange sum of a site is then added in a fixed
  * order (links into the plane below, its own plane, the plane above), so
  * trajectories agree with the two-launch step to rounding, not bit for
  * bit.  Call after sllg_set_neighbours; a new
@@ -363,8 +364,9 @@ sllg_status sllg_hysteresis(sllg_system *sys, const double *H, int64_t n_points,
  * keeps the fastest and writes its time per step (us) to *us_per_step (may
  * be NULL).  With the fused step active ("fused_active" 1) the candidates
  * are the eight fused shapes (tile, planes per item, threads per
- * workgroup) the occupancy and traffic model ranks best; otherwise every
- * tile size of the two-launch step ("tile_sites": 512, 1024, 2048 in FP32;
+ * workgroup) the occupancy and traffic model ranks best; with the brick
+ * step ("brick_active" 1), which has one shape, the XCD mapping and the steps
+ * per graph; otherwise every tile size of the two-launch step ("tile_sites": 512, 1024, 2048 in FP32;
  * 512, 1024 in FP64), each with its launch shapes ("lds_window" 1 or 0;
  * "tile_order" 1 or 0; XCD mappings 0, 1, 2 of "xcd_remap"; 1/2, 1 or 2
  * resident grids of workgroups per launch).  Systems under 2^20 spins also
@@ -465,9 +467,13 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  *                     on them; the spins are kept)
  *   "fused"           1 (default): integrate with the fused step when the
  *                     system qualifies (sllg_set_lattice) and has at least
- *                     2^20 spins (smaller systems run faster with the
- *                     two-launch step's shallow launches); 2: whenever it
- *                     qualifies; 0: always the two-launch step
+ *                     2^20 spins; smaller systems take the brick step where
+ *                     their lattice has the simple-cubic or bcc links and at
+ *                     least 5 cells on each periodic axis (with second
+ *                     neighbours up to 270,000 spins in FP32, 165,000 in
+ *                     FP64), else the two-launch step; 2: the fused step
+ *                     whenever the system qualifies; 0: always the
+ *                     two-launch step
  *   "fused_tile_x", "fused_tile_y", "fused_planes", "fused_threads"
  *                     shape of the fused step's work items: a tile of
  *                     tile_x x tile_y cell columns marched through `planes`
@@ -488,7 +494,7 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  * queued work);
  * "lattice": 0 none declared, 1 declared, 2 declared and the fused step can
  * take its structure; "fused_active": 1 when the next integration runs the
- * fused step; the fused_* shape keys read the shape in use;
+ * fused step; "brick_active": 1 when it runs the brick step; the fused_* shape keys read the shape in use;
  * "halo": neighbours with |column - row| up to this many
  * sites are read from the tile's window in LDS, the rest from HBM (-1 unset).
  */

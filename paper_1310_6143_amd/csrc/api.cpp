@@ -75,6 +75,8 @@ struct Engine {
     virtual int64_t rec_cap() = 0;
     // fused plane-marching step
     virtual void set_fused(bool on) = 0;
+    virtual void set_brick(bool on) = 0;
+    virtual bool brick_capable() = 0;          // the replica can take the brick step
     virtual bool fused_capable() = 0;          // the replica can take the fused step
     virtual FusedShape fused_shape() = 0;
     virtual void set_fused_shape(const FusedShape& f) = 0;
@@ -167,16 +169,18 @@ struct EngineT final : Engine {
     }
     int64_t rec_cap() override { return cap; }
     void set_fused(bool on) override { batch.set_fused(on); }
+    void set_brick(bool on) override { batch.set_brick(on); }
+    bool brick_capable() override { return batch.brick_capable(q); }
     bool fused_capable() override
     {
-        return (batch.mirror(q).flags & kFused) && batch.mirror(q).f_partials;
+        return (batch.mirror(q).flags & kFused) && batch.lattice(q).on;
     }
     FusedShape fused_shape() override { return batch.fused_shape(q); }
     void set_fused_shape(const FusedShape& f) override { batch.set_fused_shape(q, f); }
     size_t lds_limit() override { return batch.lds_limit(); }
     std::vector<FusedShape> fused_candidates(int max_count) override
     {
-        if (!batch.mirror(q).f_partials)
+        if (!batch.lattice(q).on)
             return {};
         return batch.fused_candidate_shapes(q, max_count);
     }
@@ -274,14 +278,33 @@ void ensure_device(sllg_system* s)
     hip_check(hipStreamCreateWithFlags(&s->own, hipStreamNonBlocking), "hipStreamCreate");
 }
 
-// Spins from which the fused step is the default (below it the two-launch
-// step's shallow launches win: measured on bcc blocks, 0.52M spins 24.0
-// against 21.2 us per step, 1.77M spins 40.8 against 52.4 us).
+// Spins from which the fused step is the default (below it shallow launches
+// win: measured per step, FP32, bcc with second neighbours, 0.52M spins 23.7
+// against 25.3 us of the two-launch step, 1.02M 37.9 against 39.2; nearest
+// neighbours alone, 1.02M spins 32.4 against 23.0 us of the brick step, which
+// the plane march passes between 1.4M and 2M spins).
 constexpr int64_t kFusedMinSpins = int64_t(1) << 20;
 
 bool fused_wanted(const sllg_system* s)
 {
     return s->opt_fused == 2 || (s->opt_fused == 1 && s->n >= kFusedMinSpins);
+}
+
+// Whether the brick step is the default for a lattice of n spins (option
+// "fused" = 1; 0 takes the two-launch step, 2 the plane march): below the
+// fused step's size, and with second neighbours only while a launch is bound
+// by its latencies.  There the bricks' neighbours (2.4 predictors per site
+// against 1.8 to 2) make the arithmetic count early: measured per step
+// against the two-launch step, FP32 9.1 and 15.0 us at 128,000 spins, 15.0
+// and 17.3 at 221,184, 21.2 and 20.6 at 351,232; FP64 13.9 and 17.5 at
+// 128,000, 24.4 and 21.6 at 221,184.  With nearest neighbours it wins over
+// the whole range (FP32 4.7 against 12.8 us at 65,536 bcc spins, 23.0 against
+// 35.6 at 1,024,000; FP64 6.7 and 16.0, 47.9 and 69.4).
+bool brick_wanted(const sllg_system* s)
+{
+    if (s->opt_fused != 1 || fused_wanted(s))
+        return false;
+    return s->st.lat.kind != kKindBcc14 || s->n <= (s->prec == SLLG_FP32 ? 270000 : 165000);
 }
 
 Engine& engine(sllg_system* s)
@@ -301,6 +324,7 @@ Engine& engine(sllg_system* s)
         s->eng->set_tile_order((int)s->opt_tile_order, (int)s->opt_tile_group);
         s->eng->set_window(s->opt_lds_window != 0);
         s->eng->set_fused(fused_wanted(s));
+        s->eng->set_brick(brick_wanted(s));
         const FusedShape& f = s->opt_fshape;
         if (f.px > 0 && f.py > 0 && f.planes > 0 && f.bt > 0 && s->eng->fused_capable())
             s->eng->set_fused_shape(f);
@@ -638,6 +662,11 @@ double autotune(sllg_system* s, int trial_steps, hipStream_t st)
         for (const FusedShape& f : e.fused_candidates(s->prec == SLLG_FP64 ? 12 : 8))
             for (int64_t g : graphs)
                 cands.push_back({1, 100, g, 1, 1, 1, f});
+    } else if (brick_wanted(s) && e.brick_capable()) {
+        // the brick step has one shape; its XCD mapping and the chunk length vary
+        for (int remap : {1, 0})
+            for (int64_t g : graphs)
+                cands.push_back({remap, s->opt_grid_scale_pct, g, s->opt_tile_order, s->opt_lds_window, 0, FusedShape{}});
     } else {
         for (int64_t window : {1, 0})
             for (int64_t order : {1, 0})
@@ -753,7 +782,14 @@ FusedShape current_fused_shape(const sllg_system* s)
 bool fused_will_run(const sllg_system* s)
 {
     return fused_wanted(s) && fused_precision_ok(s->st.lat, s->n, s->prec == SLLG_FP32 ? 4 : 8) && s->has_mat &&
-           !s->mat.per_site_material && !s->mat.per_site_axis && !s->st.tensor && !s->mat.cubic && !s->st.demag.on;
+           plain_interactions(s->st, s->mat);
+}
+
+// The next integration takes the brick step.
+bool brick_will_run(const sllg_system* s)
+{
+    return brick_wanted(s) && brick_lattice_ok(s->st.lat, s->n, s->prec == SLLG_FP32 ? 4 : 8) && s->has_mat &&
+           plain_interactions(s->st, s->mat);
 }
 
 void apply_dynamics(sllg_system* s)
@@ -1432,8 +1468,8 @@ void set_tile_request(sllg_system* sys, int64_t value)
 double autotune_with_tiles(sllg_system* s, int trial_steps, hipStream_t st)
 {
     Engine& e0 = engine(s);
-    if (fused_wanted(s) && e0.fused_capable())
-        return autotune(s, trial_steps, st);
+    if ((fused_wanted(s) && e0.fused_capable()) || (brick_wanted(s) && e0.brick_capable()))
+        return autotune(s, trial_steps, st);   // neither runs the two-launch tiles
     const int64_t largest = s->prec == SLLG_FP64 ? tile_sites<double>() : tile_sites<float>();
     struct Best {
         double us = 1e30;
@@ -1601,8 +1637,10 @@ sllg_status sllg_set_option(sllg_system* sys, const char* key, int64_t value)
             if (value < 0 || value > 2)
                 fail(SLLG_E_ARG, "fused must be 0, 1 or 2");
             sys->opt_fused = value;
-            if (sys->eng)
+            if (sys->eng) {
                 sys->eng->set_fused(fused_wanted(sys));
+                sys->eng->set_brick(brick_wanted(sys));
+            }
         } else if (k == "fused_tile_x" || k == "fused_tile_y" || k == "fused_planes" || k == "fused_threads") {
             if (value < 0 || value > 0xFFFF)
                 fail(SLLG_E_ARG, k + " must be in 0..65535");
@@ -1688,6 +1726,8 @@ sllg_status sllg_get_option(const sllg_system* sys, const char* key, int64_t* va
         *value = sys->st.lat.on ? (sys->st.lat.fusable ? 2 : 1) : 0;
     else if (k == "fused_active")
         *value = fused_will_run(sys) ? 1 : 0;
+    else if (k == "brick_active")
+        *value = brick_will_run(sys) ? 1 : 0;
     else if (k == "fused_tile_x" || k == "fused_tile_y" || k == "fused_planes" || k == "fused_threads") {
         const FusedShape f = current_fused_shape(sys);
         *value = k == "fused_tile_x" ? f.px - 2 : k == "fused_tile_y" ? f.py - 2 : k == "fused_planes" ? f.planes : f.bt;

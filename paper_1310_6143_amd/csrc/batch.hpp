@@ -252,6 +252,14 @@ inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds
     return out;
 }
 
+// Bricks of a lattice (brick step).
+inline int64_t brick_items(const HostLattice& L)
+{
+    int c[3];
+    brick_cells(L.kind, c);
+    return (int64_t)((L.nx + c[0] - 1) / c[0]) * ((L.ny + c[1] - 1) / c[1]) * ((L.nz + c[2] - 1) / c[2]);
+}
+
 // Bytes of device memory one replica needs (used for admission).
 inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size_t real_bytes,
                             int64_t rec_cap, int avg_cap)
@@ -284,6 +292,8 @@ inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size
             ent += p.size();
         b += r(ent * sizeof(FusedEntry)) + r(s.lat.pats.size() * 16) + r(s.lat.plane_pat.size()) +
              r((size_t)fused_item_cap(s.lat) * 64);
+    } else if (plain_interactions(s, m) && brick_lattice_ok(s.lat, s.n, real_bytes)) {
+        b += r((size_t)brick_items(s.lat) * 64);
     }
     b += r(m.mat_mu.size() * sizeof(MaterialDev<double>));
     const size_t groups = (blocks + kGroupTiles - 1) / kGroupTiles;
@@ -367,6 +377,10 @@ public:
         FusedShape fshape;
         int64_t f_cap_items = 0;                // items the partials buffer holds
         std::vector<FusedItem> f_items;
+        // brick step: the lattice's kind (0: the replica cannot take it), its
+        // bricks in site order and then its record item
+        int b_kind = 0;
+        std::vector<FusedItem> b_items;
     };
 
     Batch(int device, Allocator* alloc, int max_replicas)
@@ -410,6 +424,10 @@ public:
         (void)hipFree(d_reps_);
         (void)hipFree(d_work_);
         (void)hipFree(d_fwork_);
+        for (BrickList& b : brick_) {
+            (void)hipFree(b.d);
+            (void)hipFree(b.table);
+        }
         (void)hipFree(d_nwork_);
         (void)hipFree(d_torque_work_);
         (void)hipFree(d_torque_);
@@ -587,12 +605,25 @@ public:
             r.f_plane = nullptr;
             r.f_partials = nullptr;
             r.f_px = r.f_py = r.f_items = 0;
+            if (plain_interactions(s, m) && brick_lattice_ok(s.lat, s.n, sizeof(R))) {
+                const HostLattice* L = &s.lat;
+                int c[3];
+                brick_cells(L->kind, c);
+                sl.b_kind = L->kind;
+                int32_t idx = 0;
+                for (int z0 = 0; z0 < L->nz; z0 += c[2])
+                    for (int y0 = 0; y0 < L->ny; y0 += c[1])
+                        for (int x0 = 0; x0 < L->nx; x0 += c[0])
+                            sl.b_items.push_back(FusedItem{q, x0, y0, z0, z0 + c[2], idx++});
+                sl.f_cap_items = idx;
+                sl.b_items.push_back(FusedItem{q, 0, 0, 0, -1, -1});
+            }
             if (fused_precision_ok(s.lat, s.n, sizeof(R))) {
                 size_t ent = 0;
                 for (const auto& p : s.lat.pats)
                     ent += p.size();
                 sl.lat = s.lat;
-                sl.f_cap_items = fused_item_cap(s.lat);
+                sl.f_cap_items = std::max(sl.f_cap_items, fused_item_cap(s.lat));
                 r.f_ent = get(std::max<size_t>(ent, 1) * sizeof(FusedEntry));
                 r.f_pat = (const int32_t*)get(s.lat.pats.size() * 16);
                 if (!s.lat.plane_pat.empty()) {
@@ -601,8 +632,9 @@ public:
                               "upload plane patterns");
                     r.f_plane = pp;
                 }
-                r.f_partials = (double*)get((size_t)sl.f_cap_items * 2 * 4 * sizeof(double));
             }
+            if (sl.f_cap_items > 0)
+                r.f_partials = (double*)get((size_t)sl.f_cap_items * 2 * 4 * sizeof(double));
             r.mat = (MaterialDev<R>*)get(m.mat_mu.size() * sizeof(MaterialDev<R>));
             r.partials = (double*)get(blocks * 4 * sizeof(double));
             const size_t groups = (blocks + kGroupTiles - 1) / kGroupTiles;
@@ -611,7 +643,7 @@ public:
             r.acc = (double*)get((size_t)sl.avg_cap * 5 * sizeof(double));
             r.flags = 0;
             fill_parameters(r, s, m, d);
-            if (r.f_partials)
+            if (sl.lat.on)
                 sl.fshape = fused_candidates(sl.lat, lds_limit(), sizeof(R),
                                              [&](const FusedShape& f) { return fused_resident(sl.lat, f); }, 1)
                                 .at(0);
@@ -682,7 +714,7 @@ public:
     {
         Slot& sl = slots_[q];
         ReplicaDev<R>& r = sl.rec;
-        if (!r.f_partials)
+        if (!sl.lat.on)
             return;
         const FusedShape f = sl.fshape;
         const HostLattice& L = sl.lat;
@@ -728,7 +760,7 @@ public:
     void set_fused_shape(int q, const FusedShape& f)
     {
         Slot& sl = slots_[q];
-        if (!sl.rec.f_partials)
+        if (!sl.lat.on)
             fail(SLLG_E_STATE, "the replica has no fused step");
         if (!fused_shape_ok(f, sl.lat, lds_limit(), sizeof(R)))
             fail(SLLG_E_ARG, "fused shape out of range");
@@ -748,6 +780,18 @@ public:
             mark_dirty();
         }
     }
+    // Brick step: for every replica that can take it, unless the whole
+    // batch runs the fused step.
+    void set_brick(bool on)
+    {
+        if (on != brick_on_) {
+            brick_on_ = on;
+            mark_dirty();
+        }
+    }
+    bool brick_capable(int q) const { return slots_[q].b_kind != 0; }
+    // every running replica takes the brick step
+    bool bricks_only() const { return grid_ == 0 && bricks_ > 0; }
     // Workgroups of the fused kernel the device holds at once for lattice L
     // in shape f: the register limit (queried once per kernel) and the LDS
     // of the compute units.
@@ -847,13 +891,6 @@ public:
                 ((r.flags & kAverage) && (!(r.flags & kRecord) || !r.acc)))
                 fail(SLLG_E_STATE, "replica flags do not match its buffers");
         }
-        for (size_t q = 0; q < slots_.size(); ++q) {
-            host_reps_[q] = slots_[q].used ? slots_[q].rec : ReplicaDev<R>{};
-            if (slots_[q].used && !window_)
-                host_reps_[q].flags |= kDirect;
-            if (!slots_[q].used)
-                host_reps_[q].nsteps = 0;
-        }
         // the work lists hold the replicas that run: rebuilt when that set changed
         std::vector<char> active(slots_.size());
         for (size_t q = 0; q < slots_.size(); ++q)
@@ -864,6 +901,17 @@ public:
             build_lists();
         active_ = active;
         lists_dirty_ = false;
+        for (size_t q = 0; q < slots_.size(); ++q) {
+            host_reps_[q] = slots_[q].used ? slots_[q].rec : ReplicaDev<R>{};
+            if (slots_[q].used && !window_)
+                host_reps_[q].flags |= kDirect;
+            if (!slots_[q].used)
+                host_reps_[q].nsteps = 0;
+            if (takes_brick(slots_[q])) {
+                host_reps_[q].flags |= kBrick;
+                host_reps_[q].f_items = (int32_t)slots_[q].b_items.size() - 1;   // less the record item
+            }
+        }
         // whether the fused step launches need the record code (the record
         // flags change without the lists); a captured chunk holds the
         // kernel variant chosen here
@@ -911,7 +959,7 @@ public:
         for (const auto& sl : slots_) {
             if (!sl.used || !fused)
                 continue;
-            if (!(sl.rec.flags & kFused) || !sl.rec.f_partials)
+            if (!(sl.rec.flags & kFused) || !sl.lat.on)
                 fused = false;
             else if ((f_nb >= 0 && f_nb != sl.lat.nb) || (f_bt >= 0 && f_bt != sl.fshape.bt) ||
                      (f_kind >= 0 && f_kind != sl.lat.kind))
@@ -921,10 +969,12 @@ public:
             f_kind = sl.lat.kind;
             f_plane = std::max(f_plane, fused_plane_bytes(sl.fshape, sl.lat.nb, sizeof(R)));
         }
-        // two-launch tiles (the Monte Carlo records take them in fused mode too)
+        build_bricks(fused);
+        // two-launch tiles of the replicas that do not take the brick step
+        // (the Monte Carlo records take them in fused mode too)
         work_.clear();
         for (size_t q = 0; q < slots_.size(); ++q)
-                if (slots_[q].used && slots_[q].rec.nsteps > 0)
+                if (slots_[q].used && slots_[q].rec.nsteps > 0 && (fused || !brick_on_ || !slots_[q].b_kind))
                     for (int32_t b : tile_order(slots_[q].rec.blocks, order_ ? slots_[q].plane_tiles : 0,
                                                 group_ > 0 ? group_
                                                            : balanced_group(slots_[q].plane_tiles, slots_[q].rec.tile)))
@@ -995,6 +1045,53 @@ public:
         hip_check(hipMemcpy(d_nwork_, &nwork, sizeof(int), hipMemcpyHostToDevice), "upload nwork");
     }
 
+    // Brick lists of the running replicas by kind, uploaded (empty when the
+    // batch runs the fused step).
+    void build_bricks(bool fused)
+    {
+        bricks_ = 0;
+        for (int kind = 1; kind < kBrickKinds; ++kind) {
+            BrickList& b = brick_[kind];
+            std::vector<FusedItem> all;
+            if (brick_on_ && !fused)
+                for (const auto& sl : slots_)
+                    if (sl.used && sl.rec.nsteps > 0 && sl.b_kind == kind)
+                        all.insert(all.end(), sl.b_items.begin(), sl.b_items.end());
+            const int n = (int)all.size();
+            if (n > 0 && !b.table) {
+                const std::vector<uint32_t> tab = brick_table(kind);
+                if (tab.empty())
+                    fail(SLLG_E_STATE, "brick table does not fit its workgroup");
+                hip_check(hipMalloc(&b.table, tab.size() * sizeof(uint32_t)), "hipMalloc(brick table)");
+                hip_check(hipMemcpy(b.table, tab.data(), tab.size() * sizeof(uint32_t), hipMemcpyHostToDevice),
+                          "upload brick table");
+                b.resident = std::max(brick_resident_blocks<R>(device_, kind) & ~7, 8);
+            }
+            if (n > b.cap) {
+                drop_graph();
+                (void)hipFree(b.d);
+                b.d = nullptr;
+                b.cap = std::max<int64_t>(n, 2 * b.cap);
+                hip_check(hipMalloc(&b.d, sizeof(FusedItem) * (size_t)b.cap + sizeof(int)), "hipMalloc(bricks)");
+            }
+            // as for the tiles: at most the resident workgroups, and always
+            // those for a changing batch (one graph serves it)
+            int grid = std::min((n + 7) & ~7, b.resident);
+            if (round_grid_ && n > 0)
+                grid = b.resident;
+            if (grid != b.grid)
+                drop_graph();
+            b.grid = grid;
+            if (b.d) {
+                if (n > 0)
+                    hip_check(hipMemcpy(b.d, all.data(), sizeof(FusedItem) * (size_t)n, hipMemcpyHostToDevice),
+                              "upload bricks");
+                hip_check(hipMemcpy(b.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
+            }
+            bricks_ += n;
+        }
+    }
+
     // Run one chunk of K launch steps; replica q advances mirror(q).nsteps
     // (<= K) steps.  With use_graph the launch sequence is captured once per
     // (K, grid) and replayed.
@@ -1002,7 +1099,7 @@ public:
     {
         sync_tables(st);
         last_stream_ = st;
-        if (grid_ > 0) {
+        if (grid_ > 0 || bricks_ > 0) {
             if (use_graph) {
                 if (!graph_exec_ || graph_K_ != K) {
                     drop_graph();
@@ -1066,8 +1163,12 @@ public:
             hip_check(launch_fused<R>(d_reps_, d_fwork_, nf, fgrid_, -1, remap_, true, true, fused_kind_, fused_nb_,
                                       fused_bt_, fused_plane_, st),
                       "measure");
-            hip_check(launch_fused_record<R>(d_reps_, (int)slots_.size(), slot, st), "record");
+            hip_check(launch_fused_record<R>(d_reps_, (int)slots_.size(), slot, kFused, st), "record");
             return;
+        }
+        if (bricks_ > 0) {
+            hip_check(enqueue_bricks(-1, true, st), "measure");
+            hip_check(launch_fused_record<R>(d_reps_, (int)slots_.size(), slot, kBrick, st), "record");
         }
         if (grid_ <= 0)
             return;
@@ -1257,14 +1358,25 @@ private:
                 e = launch_fused<R>(d_reps_, d_fwork_, nf, fgrid_, 0, remap_, true, true, fused_kind_, fused_nb_,
                                     fused_bt_, fused_plane_, st);
             if (e == hipSuccess)   // records, averaging sums and the advance
-                e = launch_fused_finish<R>(d_reps_, nrep, st);
+                e = launch_fused_finish<R>(d_reps_, nrep, kFused, st);
             return e;
         }
         for (int k = 0; k < K && e == hipSuccess; ++k) {
+            e = enqueue_bricks(k, false, st);
+            if (e != hipSuccess || grid_ <= 0)
+                continue;
             e = launch_predict<R>(d_reps_, d_work_, d_nwork_, grid_, k, remap_, false, variant_, st);
             if (e == hipSuccess)
                 e = launch_correct<R>(d_reps_, d_work_, d_nwork_, grid_, k, remap_, variant_, st);
         }
+        if (bricks_ > 0) {
+            if (e == hipSuccess)
+                e = enqueue_bricks(0, true, st);
+            if (e == hipSuccess)   // records, averaging sums and the advance
+                e = launch_fused_finish<R>(d_reps_, nrep, kBrick, st);
+        }
+        if (grid_ <= 0)
+            return e;
         if (e == hipSuccess)
             e = launch_predict<R>(d_reps_, d_work_, d_nwork_, grid_, 0, remap_, true, variant_, st);
         if (e == hipSuccess)
@@ -1275,6 +1387,19 @@ private:
             e = launch_advance<R>(d_reps_, nrep, st);
         return e;
     }
+
+    // Step k (measure: the m and E sums) of every kind's bricks.
+    hipError_t enqueue_bricks(int k, bool measure, hipStream_t st)
+    {
+        hipError_t e = hipSuccess;
+        for (int kind = 1; kind < kBrickKinds && e == hipSuccess; ++kind) {
+            const BrickList& b = brick_[kind];
+            if (b.grid > 0)
+                e = launch_brick<R>(d_reps_, b.d, b.count(), b.table, b.grid, k, remap_, measure, kind, st);
+        }
+        return e;
+    }
+    bool takes_brick(const Slot& sl) const { return sl.used && brick_on_ && !fused_mode_ && sl.b_kind != 0; }
 
     void drop_graph()
     {
@@ -1329,6 +1454,20 @@ private:
     std::vector<FusedItem> fwork_;
     FusedItem* d_fwork_ = nullptr;    // items, then their count (int) at fwork_cap_
     int64_t fwork_cap_ = 0;
+
+    // brick step: items and their count per kind, and the kind's site tables
+    static constexpr int kBrickKinds = kKindBcc14 + 1;
+    struct BrickList {
+        FusedItem* d = nullptr;   // [cap] items, then their count
+        int64_t cap = 0;
+        int grid = 0;
+        int resident = 8;
+        uint32_t* table = nullptr;
+        int* count() const { return reinterpret_cast<int*>(reinterpret_cast<char*>(d) + sizeof(FusedItem) * (size_t)cap); }
+    };
+    BrickList brick_[kBrickKinds];
+    bool brick_on_ = false;
+    int64_t bricks_ = 0;              // items listed, all kinds
 
     bool window_ = true;
     int order_ = 1;

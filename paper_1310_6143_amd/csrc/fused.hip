@@ -48,6 +48,7 @@
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "layout.hpp"
+#include "site_step.hpp"
 
 namespace sllg {
 namespace {
@@ -83,76 +84,10 @@ using FEnt = std::conditional_t<sizeof(R) == 4, FusedEntry, FusedEntryD>;
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
-// Sum of four values over the first 256 threads (fixed order: per wave, then
-// the four waves in turn); result valid in thread 0.  Every thread of the
-// block calls it.
-template <int BT>
-__device__ __forceinline__ void sum4_256(const double v[4], double out[4], double (*red)[BT / 64])
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double s = wave_sum(threadIdx.x < 256 ? v[c] : 0.0);
-        if (lane == 0 && wave < 4)
-            red[c][wave] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            out[c] = ((red[c][0] + red[c][1]) + red[c][2]) + red[c][3];
-    __syncthreads();
-}
-
-// Record `slot` of replica r from its items' sums of parity `par`: thread t
-// < 256 adds items t, t + 256, ... in order, then the fixed 256-lane sum.
-// The same order whichever kernel runs it.
-template <typename R, int BT>
-__device__ void fused_record(const ReplicaDev<R>& r, int par, int64_t slot, double (*red)[BT / 64])
-{
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    const double* p = r.f_partials + 4 * (int64_t)par * r.f_items;
-    if (threadIdx.x < 256)
-        for (int q = (int)threadIdx.x; q < r.f_items; q += 256) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                v[c] += p[4 * (int64_t)q + c];
-        }
-    double tot[4];
-    sum4_256<BT>(v, tot, red);
-    if (threadIdx.x == 0) {
-        double* out = r.records + 4 * (r.rec_pos + slot);
-        const double f = r.mu_ref * r.inv_mu_total;
-        out[0] = tot[0] * f;
-        out[1] = tot[1] * f;
-        out[2] = tot[2] * f;
-        // the Zeeman part from the summed spins: S.H_app summed over the
-        // sites is H_app.(sum of S)
-        const double zee = (double)r.H[0] * tot[0] + (double)r.H[1] * tot[1] + (double)r.H[2] * tot[2];
-        out[3] = -r.mu_ref * (tot[3] + zee);
-    }
-}
-
 __device__ __forceinline__ int wrap_cell(int u, int n)
 {
     const int m = u % n;
     return m < 0 ? m + n : m;
-}
-
-// m and E terms of one site: S and S.H_ex/2 + (k_u/mu_s)(S.e)^2, with se =
-// S.e as the predictor forms it (-E_i/mu_s is that plus S.H_app, which the
-// record adds from the summed spins).  A replica takes the fused step only
-// with one material, so mu_s is the reference moment and every site weighs
-// 1.  Written with explicit fmas so that the step and the measuring launch
-// round alike.
-template <typename R>
-__device__ __forceinline__ void record_terms(const MaterialDev<R>& m, const V3<R>& s, R se, const V3<R>& hex, R t[4])
-{
-    const R sh = fma(s.z, hex.z, fma(s.y, hex.y, s.x * hex.x));
-    t[0] = s.x;
-    t[1] = s.y;
-    t[2] = s.z;
-    t[3] = fma((R)0.5, sh, m.ku_mu * se * se);
 }
 
 // The terms of one cell (its basis sites added in R, in basis order) into
@@ -371,7 +306,6 @@ __device__ __forceinline__ void plane_step(const ReplicaDev<R>& r, const ItemGeo
     const int z0 = run.z0, z1 = run.z1;
     const R kj[2] = {r.f_kj[0], r.f_kj[1]};
     const V3<R> e{m.axis[0], m.axis[1], m.axis[2]};
-    const V3<R> Happ{r.H[0], r.H[1], r.H[2]};
     const int zp = q - 1;
     const bool zp_exists = zper || (zp >= 0 && zp < nz);
     const bool zp_need = zp >= z0 - 1 && zp <= z1 && zp_exists;
@@ -448,16 +382,9 @@ __device__ __forceinline__ void plane_step(const ReplicaDev<R>& r, const ItemGeo
                 R gn[3] = {0, 0, 0};
                 if (m.sigma != (R)0)
                     thermal_normals(r.seed, run.step, g.col + (uint32_t)b + g.plane_sites * (uint32_t)zw_m1, gn);
-                // thermal plus applied field, held for the corrector
-                const V3<R> tha{fma(m.sigma, gn[0], Happ.x), fma(m.sigma, gn[1], Happ.y),
-                                fma(m.sigma, gn[2], Happ.z)};
-                const R as = m.ani * se;
-                const V3<R> h{fma(as, e.x, hex.x) + tha.x, fma(as, e.y, hex.y) + tha.y, fma(as, e.z, hex.z) + tha.z};
-                const V3<R> ds = llg_step(s, h, r.gdt, r.alpha);
-                const V3<R> spn = normalised(V3<R>{s.x + ds.x, s.y + ds.y, s.z + ds.z});
-                cs.c_th[S1][b] = tha;
+                V3<R> spn;
+                predict_site(r, m, e, s, hex, se, gn, cs.c_th[S1][b], spn, cs.c_base[S1][b]);
                 cs.c_sp[S1][b] = spn;
-                cs.c_base[S1][b] = V3<R>{s.x + (R)0.5 * ds.x, s.y + (R)0.5 * ds.y, s.z + (R)0.5 * ds.z};
                 slot_store<R, ZOFF>(sp + g.own(b), spn);
             }
         }
@@ -498,15 +425,7 @@ __device__ __forceinline__ void plane_step(const ReplicaDev<R>& r, const ItemGeo
         for (int b = 0; b < NB; ++b) {
             // E: corrector of plane q - 2
             if (zc_own) {
-                const V3<R> s = cs.c_sp[S0][b];
-                const R as = m.ani * dot(s, e);
-                const V3<R> h{fma(as, e.x, cs.hc[S0][b].x) + cs.c_th[S0][b].x,
-                              fma(as, e.y, cs.hc[S0][b].y) + cs.c_th[S0][b].y,
-                              fma(as, e.z, cs.hc[S0][b].z) + cs.c_th[S0][b].z};
-                // half the step's dS' dt (a step of dt / 2: the halving is exact)
-                const V3<R> dsh = llg_step(s, h, (R)0.5 * r.gdt, r.alpha);
-                const V3<R> sn = normalised(V3<R>{cs.c_base[S0][b].x + dsh.x, cs.c_base[S0][b].y + dsh.y,
-                                                  cs.c_base[S0][b].z + dsh.z});
+                const V3<R> sn = correct_site(r, m, e, cs.c_sp[S0][b], cs.hc[S0][b], cs.c_th[S0][b], cs.c_base[S0][b]);
                 // ordinary stores: the L2 merges the lanes' 12- or 24-byte
                 // spins into whole lines (streaming stores of FP64 spins
                 // reached memory as 1.4 times their bytes, for no gain in time)
@@ -774,28 +693,29 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(sizeof(R) ==
         }
         // items' sums of the previous launch -> the record two steps back
         if (REC && !MEASURE && w.idx == 0 && (r.flags & kRecord) && k >= 2)
-            fused_record<R, BT>(r, (k - 1) & 1, k - 2, red);
+            item_record<R, BT>(r, (k - 1) & 1, k - 2, red);
         fused_item<R, KIND, NB, BT, MEASURE, REC>(r, w, k, fused_lds, plane_bytes, pat, ent, red, acc, dcol);
     }
 }
 
-// After the measuring launch, one workgroup per replica: the last two
+// After the measuring launch, one workgroup per replica whose flags hold
+// `which` (kFused or kBrick, the step that ran): the last two
 // records of the chunk, the averaging sums of its records, then the step
 // counter, parity and record position advance (one launch for the chunk's
 // end instead of three).
 template <typename R>
-__global__ __launch_bounds__(256) void k_fused_finish(ReplicaDev<R>* __restrict__ reps)
+__global__ __launch_bounds__(256) void k_fused_finish(ReplicaDev<R>* __restrict__ reps, int32_t which)
 {
     __shared__ double red[4][4];
     ReplicaDev<R>& r = reps[blockIdx.x];
-    if (r.nsteps <= 0)
+    if (r.nsteps <= 0 || !(r.flags & which))
         return;   // uniform over the block
-    if ((r.flags & kFused) && (r.flags & kRecord)) {
+    if (r.flags & kRecord) {
         if (r.nsteps >= 2)
-            fused_record<R, 256>(r, (r.nsteps - 1) & 1, r.nsteps - 2, red);
-        fused_record<R, 256>(r, r.nsteps & 1, r.nsteps - 1, red);
+            item_record<R, 256>(r, (r.nsteps - 1) & 1, r.nsteps - 2, red);
+        item_record<R, 256>(r, r.nsteps & 1, r.nsteps - 1, red);
     }
-    // thread 0 wrote the records (fused_record) and reads them back here
+    // thread 0 wrote the records (item_record) and reads them back here
     if (threadIdx.x == 0) {
         accumulate_records(r);
         advance_replica(r);
@@ -806,13 +726,13 @@ __global__ __launch_bounds__(256) void k_fused_finish(ReplicaDev<R>* __restrict_
 // replica: the items' sums into record `slot` (Monte Carlo records; no
 // advance of the step counter or parity).
 template <typename R>
-__global__ __launch_bounds__(256) void k_fused_record(ReplicaDev<R>* __restrict__ reps, int slot)
+__global__ __launch_bounds__(256) void k_fused_record(ReplicaDev<R>* __restrict__ reps, int slot, int32_t which)
 {
     __shared__ double red[4][4];
     const ReplicaDev<R>& r = reps[blockIdx.x];
-    if (r.nsteps <= 0 || !(r.flags & kFused) || !(r.flags & kRecord))
+    if (r.nsteps <= 0 || !(r.flags & which) || !(r.flags & kRecord))
         return;   // uniform over the block
-    fused_record<R, 256>(r, 0, slot, red);
+    item_record<R, 256>(r, 0, slot, red);
 }
 
 // The measuring launch always records; a step launch records unless no
@@ -894,20 +814,20 @@ hipError_t launch_fused(const ReplicaDev<R>* reps, const FusedItem* items, const
 }
 
 template <typename R>
-hipError_t launch_fused_finish(ReplicaDev<R>* reps, int n_rep, hipStream_t st)
+hipError_t launch_fused_finish(ReplicaDev<R>* reps, int n_rep, int32_t which, hipStream_t st)
 {
     if (n_rep <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL((k_fused_finish<R>), dim3(n_rep), dim3(256), 0, st, reps);
+    hipLaunchKernelGGL((k_fused_finish<R>), dim3(n_rep), dim3(256), 0, st, reps, which);
     return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_fused_record(ReplicaDev<R>* reps, int n_rep, int slot, hipStream_t st)
+hipError_t launch_fused_record(ReplicaDev<R>* reps, int n_rep, int slot, int32_t which, hipStream_t st)
 {
     if (n_rep <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL((k_fused_record<R>), dim3(n_rep), dim3(256), 0, st, reps, slot);
+    hipLaunchKernelGGL((k_fused_record<R>), dim3(n_rep), dim3(256), 0, st, reps, slot, which);
     return hipGetLastError();
 }
 
@@ -937,10 +857,10 @@ template hipError_t launch_fused<float>(const ReplicaDev<float>*, const FusedIte
                                         bool, int, int, int, int, hipStream_t);
 template hipError_t launch_fused<double>(const ReplicaDev<double>*, const FusedItem*, const int*, int, int, int, bool,
                                          bool, int, int, int, int, hipStream_t);
-template hipError_t launch_fused_finish<float>(ReplicaDev<float>*, int, hipStream_t);
-template hipError_t launch_fused_finish<double>(ReplicaDev<double>*, int, hipStream_t);
-template hipError_t launch_fused_record<float>(ReplicaDev<float>*, int, int, hipStream_t);
-template hipError_t launch_fused_record<double>(ReplicaDev<double>*, int, int, hipStream_t);
+template hipError_t launch_fused_finish<float>(ReplicaDev<float>*, int, int32_t, hipStream_t);
+template hipError_t launch_fused_finish<double>(ReplicaDev<double>*, int, int32_t, hipStream_t);
+template hipError_t launch_fused_record<float>(ReplicaDev<float>*, int, int, int32_t, hipStream_t);
+template hipError_t launch_fused_record<double>(ReplicaDev<double>*, int, int, int32_t, hipStream_t);
 template int fused_resident_blocks<float>(int, int, int, int, int);
 template int fused_resident_blocks<double>(int, int, int, int, int);
 

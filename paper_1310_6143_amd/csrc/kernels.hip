@@ -787,8 +787,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_finish(const ReplicaDev<R>* _
 {
     __shared__ double red[4][kWaves];
     const ReplicaDev<R>& r = reps[blockIdx.x];
-    if (!(r.flags & kRecord) || (mode == 0 && r.nsteps <= 0))
-        return;
+    if (!(r.flags & kRecord) || (mode == 0 && (r.nsteps <= 0 || (r.flags & kBrick))))
+        return;   // a brick chunk's records come from its own items
     const int n_groups = (r.blocks + kGroupTiles - 1) / kGroupTiles;
     for (int g = 0; g < n_groups; ++g)
         group_reduce(r, g, red);
@@ -1012,7 +1012,7 @@ template <typename R>
 __global__ void k_advance(ReplicaDev<R>* __restrict__ reps, int n_rep)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n_rep)
+    if (j < n_rep && !(reps[j].flags & kBrick))
         advance_replica(reps[j]);
 }
 
@@ -1231,7 +1231,7 @@ template <typename R>
 __global__ void k_accumulate(const ReplicaDev<R>* __restrict__ reps, int n_rep)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n_rep)
+    if (j < n_rep && !(reps[j].flags & kBrick))
         accumulate_records(reps[j]);
 }
 

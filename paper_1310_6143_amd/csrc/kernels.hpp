@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 #include "layout.hpp"
 
@@ -86,16 +87,17 @@ hipError_t launch_mc(const ReplicaDev<R>* rep, const int32_t* sites, const uint1
 template <typename R>
 hipError_t launch_fused(const ReplicaDev<R>* reps, const FusedItem* items, const int* n_items, int grid, int k,
                         int remap, bool measure, bool rec, int kind, int nb, int bt, int plane_bytes, hipStream_t st);
-// The end of a fused chunk for every replica: its last two records (when
+// The end of a fused or brick chunk for every replica whose flags hold
+// `which` (kFused or kBrick): its last two records (when
 // recording), the averaging sums of its records, and the advance of the
 // step counter, parity and record position.
 template <typename R>
-hipError_t launch_fused_finish(ReplicaDev<R>* reps, int n_rep, hipStream_t st);
-// Monte Carlo records on the fused step's items: after launch_fused with
-// measure and k = -1 (the current state, in place), the items' sums of
+hipError_t launch_fused_finish(ReplicaDev<R>* reps, int n_rep, int32_t which, hipStream_t st);
+// Monte Carlo records on the fused step's or the brick step's items (`which`
+// as above): after launch_fused or launch_brick with measure and k = -1 (the current state, in place), the items' sums of
 // every recording replica into record `slot`.
 template <typename R>
-hipError_t launch_fused_record(ReplicaDev<R>* reps, int n_rep, int slot, hipStream_t st);
+hipError_t launch_fused_record(ReplicaDev<R>* reps, int n_rep, int slot, int32_t which, hipStream_t st);
 // Resident workgroups of the fused kernel (kind, nb, bt) per device with
 // plane_bytes LDS planes; 0 if unknown.
 template <typename R>
@@ -108,6 +110,19 @@ size_t fused_lds_bytes(int kind, int plane_bytes, int bt);
 // Static LDS of a fused workgroup of bt threads (its FP64 sums, copy table
 // and reduction slots).
 size_t fused_static_lds(int bt, size_t real_bytes);
+
+// Brick step (brick.hip) of step k over the bricks of every listed replica
+// of one compiled kind: one launch per Heun step; measure: the m and E sums
+// of the state after the chunk (k >= 0) or of the current state (k < 0).
+// table: brick_table(kind) in device memory.
+template <typename R>
+hipError_t launch_brick(const ReplicaDev<R>* reps, const FusedItem* items, const int* n_items, const uint32_t* table,
+                        int grid, int k, int remap, bool measure, int kind, hipStream_t st);
+template <typename R>
+int brick_resident_blocks(int device, int kind);
+// Site tables of a kind's brick, and the brick's cells per axis.
+std::vector<uint32_t> brick_table(int kind);
+void brick_cells(int kind, int cells[3]);
 
 // LDS planes of the fused step for a thread region of px x py cells (tile
 // plus ring) with nb sites per cell: the region and one more ring.  FP32:

@@ -122,6 +122,7 @@ enum ReplicaFlags : int32_t {
     kDemag = 1024,          // macrocell demagnetising field dm_field[dm_cell[i]] added to every site
     kLongRows = 2048,       // SELL rows longer than kLongRow links: batched gathers (general variant)
     kFused = 4096,          // the lattice runs the fused plane-marching step (f_* fields)
+    kBrick = 16384,         // this chunk runs the brick step (set in the device table only)
     kWide = 8192,           // neighbours in the wide stencil form (w_pid / w_tab in global memory)
 };
 
@@ -146,6 +147,9 @@ constexpr int kFusedMaxPatterns = 64;     // distinct (plane class, basis site) 
 constexpr int kFusedMaxEntries = 1024;    // entries of all patterns together
 constexpr int kFusedMaxBasis = 2;         // sites per cell the fused kernels are built for
 constexpr int kFusedMinEdge = 8;          // smallest thread region per axis (cells)
+// Brick step: fewest cells on a periodic axis (a brick's box reaches at most
+// 9 cells past the lattice edge, unwrapped by two subtractions).
+constexpr int kBrickMinEdge = 5;
 
 // Lattice kinds the fused kernel is compiled for, so that a site's links
 // are compile-time constants (LDS offsets become instruction immediates):
@@ -199,6 +203,8 @@ struct FusedEntryD {
     double J;
 };
 
+// A work item of the fused step, or a brick of the brick step (its first
+// cell; z1 < 0: the replica's record item).
 struct FusedItem {
     int32_t replica;
     int32_t x0, y0;      // first cell of the tile (interior) on x and y

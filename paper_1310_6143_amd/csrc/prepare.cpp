@@ -798,20 +798,20 @@ void fill_parameters(ReplicaDev<R>& rec, const HostStructure& s, const HostMater
     // the fused step: a lattice it takes in this precision, uniform
     // materials, scalar exchange and no cubic anisotropy or demagnetising
     // field
-    if (fused_precision_ok(s.lat, s.n, sizeof(R)) && !m.per_site_material && !m.per_site_axis && !s.tensor &&
-        !m.cubic && !s.demag.on)
+    if (fused_precision_ok(s.lat, s.n, sizeof(R)) && plain_interactions(s, m))
         flags |= kFused;
     rec.flags = flags;
-    rec.f_nb = s.lat.nb;
-    rec.f_nx = s.lat.nx;
-    rec.f_ny = s.lat.ny;
-    rec.f_nz = s.lat.nz;
-    rec.f_zper = s.lat.per[2] ? 1 : 0;
-    rec.f_npat = (int32_t)s.lat.pats.size();
-    rec.f_kind = s.lat.kind;
+    const HostLattice& L = s.lat;
+    rec.f_nb = L.nb;
+    rec.f_nx = L.nx;
+    rec.f_ny = L.ny;
+    rec.f_nz = L.nz;
+    rec.f_zper = L.per[2] ? 1 : 0;
+    rec.f_npat = (int32_t)L.pats.size();
+    rec.f_kind = L.kind;
     rec.f_pad = 0;
     for (int q = 0; q < 2; ++q)
-        rec.f_kj[q] = s.lat.on ? rec.jt[s.lat.slot_type[q]] : (R)0;
+        rec.f_kj[q] = L.on ? rec.jt[L.slot_type[q]] : (R)0;
     int32_t nent = 0;
     for (const auto& p : s.lat.pats)
         nent += (int32_t)p.size();

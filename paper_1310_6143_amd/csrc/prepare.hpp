@@ -147,6 +147,15 @@ struct HostStructure {
     HostLattice lat;
 };
 
+// Whether the brick step is built for lattice L of n sites in a precision
+// (bytes per real): a compiled kind with at least kBrickMinEdge cells per
+// periodic axis whose spins have 31-bit byte offsets.
+inline bool brick_lattice_ok(const HostLattice& L, int64_t n, size_t real_bytes)
+{
+    return L.on && L.fusable && L.kind != kKindGeneric && L.nx >= kBrickMinEdge && L.ny >= kBrickMinEdge &&
+           (!L.per[2] || L.nz >= kBrickMinEdge) && n * 3 * (int64_t)real_bytes + 16 <= 0x7FFFFFFF;
+}
+
 // Declares the structure's sites as a lattice of nb sites per cell on
 // cells[0] x cells[1] x cells[2] cells (periodic[a] != 0: periodic axis) and
 // derives the fused step's link patterns.  Throws Failure(SLLG_E_ARG) when
@@ -233,6 +242,14 @@ std::vector<MaterialDev<R>> material_table(const HostMaterials& m, const Dynamic
 template <typename R>
 void fill_parameters(ReplicaDev<R>& rec, const HostStructure& s, const HostMaterials& m,
                      const Dynamics& d);
+
+// Whether a replica can take the fused and brick steps as far as its
+// interactions go: one material, scalar exchange, no cubic anisotropy or
+// demagnetising field.
+inline bool plain_interactions(const HostStructure& s, const HostMaterials& m)
+{
+    return !m.per_site_material && !m.per_site_axis && !s.tensor && !m.cubic && !s.demag.on;
+}
 
 // Thermal averages from per-block sums acc[b][5] = sums of (|m|, m_x, m_y,
 // m_z, E) over block_len samples each: out = { <|m|>, se, <m_x>, <m_y>,
