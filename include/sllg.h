@@ -470,8 +470,11 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  *                     2^20 spins; smaller systems take the brick step where
  *                     their lattice has the simple-cubic or bcc links and at
  *                     least 5 cells on each periodic axis (with second
- *                     neighbours up to 270,000 spins in FP32, 165,000 in
- *                     FP64), else the two-launch step; 2: the fused step
+ *                     neighbours up to 150,000 spins in FP32, 100,000 in
+ *                     FP64) and the sites of a class (basis site, first,
+ *                     inner or last cell of each axis) list their links in
+ *                     one order, with the spins of the two-launch step bit
+ *                     for bit, else the two-launch step; 2: the fused step
  *                     whenever the system qualifies; 0: always the
  *                     two-launch step
  *   "fused_tile_x", "fused_tile_y", "fused_planes", "fused_threads"

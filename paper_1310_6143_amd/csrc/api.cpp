@@ -281,8 +281,7 @@ void ensure_device(sllg_system* s)
 // Spins from which the fused step is the default (below it shallow launches
 // win: measured per step, FP32, bcc with second neighbours, 0.52M spins 23.7
 // against 25.3 us of the two-launch step, 1.02M 37.9 against 39.2; nearest
-// neighbours alone, 1.02M spins 32.4 against 23.0 us of the brick step, which
-// the plane march passes between 1.4M and 2M spins).
+// neighbours alone, 1.02M spins 32.4 against 32.0 us of the brick step).
 constexpr int64_t kFusedMinSpins = int64_t(1) << 20;
 
 bool fused_wanted(const sllg_system* s)
@@ -295,16 +294,16 @@ bool fused_wanted(const sllg_system* s)
 // fused step's size, and with second neighbours only while a launch is bound
 // by its latencies.  There the bricks' neighbours (2.4 predictors per site
 // against 1.8 to 2) make the arithmetic count early: measured per step
-// against the two-launch step, FP32 9.1 and 15.0 us at 128,000 spins, 15.0
-// and 17.3 at 221,184, 21.2 and 20.6 at 351,232; FP64 13.9 and 17.5 at
-// 128,000, 24.4 and 21.6 at 221,184.  With nearest neighbours it wins over
-// the whole range (FP32 4.7 against 12.8 us at 65,536 bcc spins, 23.0 against
-// 35.6 at 1,024,000; FP64 6.7 and 16.0, 47.9 and 69.4).
+// against the two-launch step, FP32 8.8 and 14.3 us at 65,536 spins, 13.4
+// and 15.0 at 128,000, 24.0 and 17.2 at 221,184; FP64 12.4 and 17.2 at
+// 65,536, 20.1 and 17.5 at 128,000.  With nearest neighbours it wins over
+// the whole range (FP32 5.3 against 13.0 us at 65,536 bcc spins, 32.0 against
+// 35.6 at 1,024,000; FP64 7.3 and 16.0, 55.3 and 69.3).
 bool brick_wanted(const sllg_system* s)
 {
     if (s->opt_fused != 1 || fused_wanted(s))
         return false;
-    return s->st.lat.kind != kKindBcc14 || s->n <= (s->prec == SLLG_FP32 ? 270000 : 165000);
+    return s->st.lat.kind != kKindBcc14 || s->n <= (s->prec == SLLG_FP32 ? 150000 : 100000);
 }
 
 Engine& engine(sllg_system* s)
@@ -788,7 +787,7 @@ bool fused_will_run(const sllg_system* s)
 // The next integration takes the brick step.
 bool brick_will_run(const sllg_system* s)
 {
-    return brick_wanted(s) && brick_lattice_ok(s->st.lat, s->n, s->prec == SLLG_FP32 ? 4 : 8) && s->has_mat &&
+    return brick_wanted(s) && brick_ok(s->st, s->prec == SLLG_FP32 ? 4 : 8) && s->has_mat &&
            plain_interactions(s->st, s->mat);
 }
 

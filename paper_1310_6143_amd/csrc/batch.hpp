@@ -292,8 +292,8 @@ inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size
             ent += p.size();
         b += r(ent * sizeof(FusedEntry)) + r(s.lat.pats.size() * 16) + r(s.lat.plane_pat.size()) +
              r((size_t)fused_item_cap(s.lat) * 64);
-    } else if (plain_interactions(s, m) && brick_lattice_ok(s.lat, s.n, real_bytes)) {
-        b += r((size_t)brick_items(s.lat) * 64);
+    } else if (plain_interactions(s, m) && brick_ok(s, real_bytes)) {
+        b += r((size_t)brick_items(s.lat) * 64) + r(s.brick_words.size() * 4);
     }
     b += r(m.mat_mu.size() * sizeof(MaterialDev<double>));
     const size_t groups = (blocks + kGroupTiles - 1) / kGroupTiles;
@@ -600,12 +600,13 @@ public:
                 r.dm_field = df;
                 r.dm_part = dpart;
             }
+            r.b_links = nullptr;
             r.f_ent = nullptr;
             r.f_pat = nullptr;
             r.f_plane = nullptr;
             r.f_partials = nullptr;
             r.f_px = r.f_py = r.f_items = 0;
-            if (plain_interactions(s, m) && brick_lattice_ok(s.lat, s.n, sizeof(R))) {
+            if (plain_interactions(s, m) && brick_ok(s, sizeof(R))) {
                 const HostLattice* L = &s.lat;
                 int c[3];
                 brick_cells(L->kind, c);
@@ -617,6 +618,10 @@ public:
                             sl.b_items.push_back(FusedItem{q, x0, y0, z0, z0 + c[2], idx++});
                 sl.f_cap_items = idx;
                 sl.b_items.push_back(FusedItem{q, 0, 0, 0, -1, -1});
+                uint32_t* words = (uint32_t*)get(s.brick_words.size() * 4);
+                hip_check(hipMemcpy(words, s.brick_words.data(), s.brick_words.size() * 4, hipMemcpyHostToDevice),
+                          "upload brick links");
+                r.b_links = words;
             }
             if (fused_precision_ok(s.lat, s.n, sizeof(R))) {
                 size_t ent = 0;

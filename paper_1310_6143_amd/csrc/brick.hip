@@ -19,11 +19,16 @@
 // run on the waves that have no corrector to do.  The plane-marching step
 // (fused.hip) recomputes less per site but walks its planes in series.
 // Measured per step (FP32, 300 K, records every step, two-launch step before):
-// 4,096 simple-cubic spins 12.7 -> 4.5 us, 262,144 15.0 -> 7.8, 65,536 bcc
-// spins 12.8 -> 4.7, 524,288 22.9 -> 14.1; FP64 16.4 -> 5.9, 19.4 -> 14.0,
-// 16.0 -> 6.7 and 35.5 -> 24.7.
-// The formulas and the order of every sum are those of fused.hip, so the
-// spins do not depend on which of the two steps runs or on the brick.
+// 4,096 simple-cubic spins 12.7 -> 5.1 us, 262,144 15.2 -> 9.0, 65,536 bcc
+// spins 13.0 -> 5.3, 524,288 23.1 -> 17.0; FP64 16.5 -> 6.8, 19.7 -> 16.7,
+// 16.0 -> 7.3 and 35.5 -> 28.8.
+// The terms, their order and the formulas are those of the two-launch step
+// (kernels.hip), so the spins are the same bits whichever of the two runs.
+// For that a site's links come from a table by class (basis site, first,
+// inner or last cell on each axis) that holds its row's order, not from the
+// kind's constants (which took 4.5 us for the 4,096 spins: FP32 trajectories
+// above room temperature part from a rounding difference by 1e-3 of a spin
+// component within 2000 steps, so one set of roundings is kept).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -53,6 +58,8 @@ struct Brick {
     static constexpr int H = KIND == kKindBcc8 ? 1 : 2;   // bcc sites reach half a cell per link
     static constexpr int SX = TX + 2 * H, SY = TY + 2 * H, SZ = TZ + 2 * H, VOL = SX * SY * SZ;
     static constexpr int OWN = NB * TX * TY * TZ;
+    static constexpr int PAIRS = brick_pairs(KIND);       // link words of a class: near, then far
+    static constexpr int WORDS = (2 * PAIRS + 3) & ~3;    // in whole 16-byte loads
     static constexpr int LOADS = (NB * VOL + BT - 1) / BT;   // table rounds (pruned entries are invalid)
     static_assert(OWN == 256, "the record sums take 256 brick sites, four waves");
     static_assert(NB * VOL <= 4096, "slots fit the table entries");
@@ -63,9 +70,9 @@ struct Brick {
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
 // x, y, z of a box slot.  FP32: 16 bytes per slot, read and written as one
-// vector (as three words the bcc kinds' reads become 4-byte ones at a
-// 16-byte stride, a fourfold bank conflict: 21.0 against 15.0 us per step on
-// 221,184 bcc spins with second neighbours).  FP64: x, y in one array and z in another.
+// vector (as three words they may become 4-byte reads at a 16-byte stride, a
+// fourfold bank conflict: 21.0 against 15.0 us per step on 221,184 bcc spins
+// with second neighbours, links by constants).  FP64: x, y in one array and z in another.
 template <typename R, int SLOTS>
 struct Box;
 template <int SLOTS>
@@ -105,40 +112,49 @@ __device__ __forceinline__ int wrap_near(int u, int n)
     return u;
 }
 
-// sum of the links of a site of basis B at slot q, in the canonical order
-// (plane below, own plane, plane above).
-template <typename R, int KIND, int B, typename BoxT>
-__device__ __forceinline__ V3<R> box_links(const BoxT& box, int q, const R kj[2])
+// Exchange sum of the site at slot q from its class's link words: the near
+// links in row order, the far ones in row order, then their sum, as the
+// two-launch step adds them (links past a class's own are padding, J = 0).
+template <typename R, int KIND, typename BoxT>
+__device__ __forceinline__ V3<R> box_links(const BoxT& box, int q, const uint32_t words[Brick<KIND>::WORDS],
+                                           int near, int far, const R kj[2])
 {
-    using G = Brick<KIND>;
-    V3<R> h{0, 0, 0};
+    constexpr int P = Brick<KIND>::PAIRS;
+    // every read of a part is issued before the first is used
+    auto part = [&](const uint32_t* w, int pairs) {
+        V3<R> v[2 * P], h{0, 0, 0};
+        auto half = [&](int k) { return k & 1 ? (int)w[k / 2] >> 16 : (int)(int16_t)(w[k / 2] & 0xFFFFu); };
 #pragma unroll
-    for (int dz = -1; dz <= 1; ++dz)
+        for (int j = 0; j < P; ++j)
+            if (j < pairs) {
+                v[2 * j] = box.get(q + (half(2 * j) >> 2));
+                v[2 * j + 1] = box.get(q + (half(2 * j + 1) >> 2));
+            }
 #pragma unroll
-        for (int dy = -1; dy <= 1; ++dy)
+        for (int j = 0; j < P; ++j)
+            if (j < pairs)
 #pragma unroll
-            for (int dx = -1; dx <= 1; ++dx)
-#pragma unroll
-                for (int bp = 0; bp < G::NB; ++bp) {
-                    int slot = 0;
-                    if (!kind_link(KIND, B, dz, dy, dx, bp, &slot))
-                        continue;
-                    const V3<R> v = box.get(q + (bp - B) * G::VOL + (dz * G::SY + dy) * G::SX + dx);
-                    h.x = fma(kj[slot], v.x, h.x);
-                    h.y = fma(kj[slot], v.y, h.y);
-                    h.z = fma(kj[slot], v.z, h.z);
+                for (int k = 2 * j; k < 2 * j + 2; ++k) {
+                    const int code = half(k) & 3;
+                    const R J = code == 0 ? kj[0] : KIND == kKindBcc14 && code == 1 ? kj[1] : (R)0;
+                    h.x = fma(J, v[k].x, h.x);
+                    h.y = fma(J, v[k].y, h.y);
+                    h.z = fma(J, v[k].z, h.z);
                 }
-    return h;
+        return h;
+    };
+    const V3<R> hn = part(words, near), hf = part(words + P, far);
+    return V3<R>{hn.x + hf.x, hn.y + hf.y, hn.z + hf.z};
 }
 
-template <typename R, int KIND, typename BoxT>
-__device__ __forceinline__ V3<R> box_links(const BoxT& box, int q, int b, const R kj[2])
+// Adds the thermal field sigma * g.
+template <typename R>
+__device__ __forceinline__ void add_thermal(const MaterialDev<R>& m, const R g[3], V3<R>& h)
 {
-    if constexpr (Brick<KIND>::NB == 1) {
-        return box_links<R, KIND, 0>(box, q, kj);
-    } else {
-        // b is the same over a wave: one of the two runs
-        return b == 0 ? box_links<R, KIND, 0>(box, q, kj) : box_links<R, KIND, 1>(box, q, kj);
+    if (m.sigma != (R)0) {
+        h.x += m.sigma * g[0];
+        h.y += m.sigma * g[1];
+        h.z += m.sigma * g[2];
     }
 }
 
@@ -180,7 +196,7 @@ __global__ __launch_bounds__(Brick<KIND>::BT) void k_brick(const ReplicaDev<R>* 
         first = false;
         if (w.z1 < 0) {
             if (!MEASURE && (flags & kRecord) && k >= 2)
-                item_record<R, BT>(r, (k - 1) & 1, k - 2, red);
+                item_record<R, BT, false>(r, (k - 1) & 1, k - 2, red);
             continue;
         }
         const int mslot = MEASURE ? (k < 0 ? 0 : nsteps) : k;
@@ -217,25 +233,50 @@ __global__ __launch_bounds__(Brick<KIND>::BT) void k_brick(const ReplicaDev<R>* 
         const MaterialDev<R> m = uniform_material(r);
         const R kj[2] = {r.f_kj[0], r.f_kj[1]};
         const V3<R> e{m.axis[0], m.axis[1], m.axis[2]};
+        const V3<R> Happ{r.H[0], r.H[1], r.H[2]};
         const bool rec = (flags & kRecord) && (MEASURE || k >= 1);
+        // its links: those of its class (basis site, first, inner or last cell
+        // of each axis)
+        uint32_t words[G::WORDS];
+        const int near = r.b_near, far = r.b_far;
+        if (exists) {
+            const int cls = b * 27 + edge_class(zw, nz) * 9 + edge_class(wrap_near(uy, ny), ny) * 3 +
+                            edge_class(wrap_near(ux, nx), nx);
+#pragma unroll
+            for (int j = 0; j < G::WORDS; j += 4) {
+                typedef uint32_t Word4 __attribute__((ext_vector_type(4)));
+                const Word4 v = gload((const Word4*)r.b_links, cls * (G::WORDS / 4) + j / 4);
+                words[j] = v.x;
+                words[j + 1] = v.y;
+                words[j + 2] = v.z;
+                words[j + 3] = v.w;
+            }
+        }
         R gn[3] = {0, 0, 0};
         if (!MEASURE && m.sigma != (R)0 && exists)
             thermal_normals(r.seed, r.step + (uint64_t)k, site, gn);
         __syncthreads();   // S complete
-        V3<R> th{0, 0, 0}, spn{0, 0, 0}, base{0, 0, 0};
+        V3<R> s0{0, 0, 0}, spn{0, 0, 0};
         if (MEASURE ? own : exists) {
-            const V3<R> s = box_s.get(q);
-            const V3<R> hex = box_links<R, KIND>(box_s, q, b, kj);
-            const R se = fma(s.z, e.z, fma(s.y, e.y, s.x * e.x));
+            s0 = box_s.get(q);
+            const V3<R> sum = box_links<R, KIND>(box_s, q, words, near, far, kj);
+            const V3<R> hex{m.mu_rel * sum.x, m.mu_rel * sum.y, m.mu_rel * sum.z};
+            const R se = dot(s0, e);
             if (rec && own) {
-                R tc[4];
-                record_terms(m, s, se, hex, tc);
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    terms[c][t] = tc[c];
+                // in units of mu_ref: mu_s/mu_ref S and mu_s/mu_ref (-E_i/mu_s)
+                const R u = (R)0.5 * dot(s0, hex) + m.ku_mu * se * se + dot(s0, Happ);
+                terms[0][t] = m.mu_frac * s0.x;
+                terms[1][t] = m.mu_frac * s0.y;
+                terms[2][t] = m.mu_frac * s0.z;
+                terms[3][t] = m.mu_frac * u;
             }
-            if (!MEASURE)
-                predict_site(r, m, e, s, hex, se, gn, th, spn, base);
+            if (!MEASURE) {
+                V3<R> h{hex.x + m.ani * se * e.x + Happ.x, hex.y + m.ani * se * e.y + Happ.y,
+                        hex.z + m.ani * se * e.z + Happ.z};
+                add_thermal(m, gn, h);
+                const V3<R> ds = llg_step(s0, h, r.gdt, r.alpha);
+                spn = normalised(V3<R>{s0.x + ds.x, s0.y + ds.y, s0.z + ds.z});
+            }
         }
         if (rec && t < G::OWN && !own)
 #pragma unroll
@@ -246,8 +287,17 @@ __global__ __launch_bounds__(Brick<KIND>::BT) void k_brick(const ReplicaDev<R>* 
         __syncthreads();   // S' and the record terms complete
         if (t < G::OWN) {
             if (!MEASURE && own) {
-                const V3<R> hc = box_links<R, KIND>(box_p, q, b, kj);
-                const V3<R> sn = correct_site(r, m, e, spn, hc, th, base);
+                const V3<R> sum = box_links<R, KIND>(box_p, q, words, near, far, kj);
+                const R se = dot(spn, e);
+                V3<R> h{m.mu_rel * sum.x + m.ani * se * e.x + Happ.x, m.mu_rel * sum.y + m.ani * se * e.y + Happ.y,
+                        m.mu_rel * sum.z + m.ani * se * e.z + Happ.z};
+                add_thermal(m, gn, h);
+                const V3<R> ds = llg_step(spn, h, r.gdt, r.alpha);
+                // this sum's order is the one the two-launch corrector is compiled to
+                const R c = (R)0.5 * recip(fma(s0.z, spn.z, fma(s0.x, spn.x, s0.y * spn.y)));
+                const V3<R> half{(R)0.5 * s0.x + c * spn.x, (R)0.5 * s0.y + c * spn.y, (R)0.5 * s0.z + c * spn.z};
+                const V3<R> sn = normalised(
+                    V3<R>{half.x + (R)0.5 * ds.x, half.y + (R)0.5 * ds.y, half.z + (R)0.5 * ds.z});
                 SLLG_GLOBAL R* dst = (SLLG_GLOBAL R*)r.S[par ^ 1] + 3 * (int64_t)site;
                 dst[0] = sn.x;
                 dst[1] = sn.y;
@@ -341,6 +391,17 @@ std::vector<uint32_t> brick_table(int kind)
     case kKindSc6: return build_table<kKindSc6>();
     case kKindBcc8: return build_table<kKindBcc8>();
     case kKindBcc14: return build_table<kKindBcc14>();
+    }
+    return {};
+}
+
+BrickBox brick_box(int kind)
+{
+    switch (kind) {
+    case kKindSc6: return {Brick<kKindSc6>::SX, Brick<kKindSc6>::SY, Brick<kKindSc6>::VOL, Brick<kKindSc6>::WORDS};
+    case kKindBcc8: return {Brick<kKindBcc8>::SX, Brick<kKindBcc8>::SY, Brick<kKindBcc8>::VOL, Brick<kKindBcc8>::WORDS};
+    case kKindBcc14:
+        return {Brick<kKindBcc14>::SX, Brick<kKindBcc14>::SY, Brick<kKindBcc14>::VOL, Brick<kKindBcc14>::WORDS};
     }
     return {};
 }

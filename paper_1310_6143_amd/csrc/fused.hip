@@ -693,7 +693,7 @@ __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(sizeof(R) ==
         }
         // items' sums of the previous launch -> the record two steps back
         if (REC && !MEASURE && w.idx == 0 && (r.flags & kRecord) && k >= 2)
-            item_record<R, BT>(r, (k - 1) & 1, k - 2, red);
+            item_record<R, BT, true>(r, (k - 1) & 1, k - 2, red);
         fused_item<R, KIND, NB, BT, MEASURE, REC>(r, w, k, fused_lds, plane_bytes, pat, ent, red, acc, dcol);
     }
 }
@@ -711,9 +711,12 @@ __global__ __launch_bounds__(256) void k_fused_finish(ReplicaDev<R>* __restrict_
     if (r.nsteps <= 0 || !(r.flags & which))
         return;   // uniform over the block
     if (r.flags & kRecord) {
-        if (r.nsteps >= 2)
-            item_record<R, 256>(r, (r.nsteps - 1) & 1, r.nsteps - 2, red);
-        item_record<R, 256>(r, r.nsteps & 1, r.nsteps - 1, red);
+        for (int k = r.nsteps >= 2 ? r.nsteps - 1 : r.nsteps; k <= r.nsteps; ++k) {
+            if (which == kBrick)
+                item_record<R, 256, false>(r, k & 1, k - 1, red);
+            else
+                item_record<R, 256, true>(r, k & 1, k - 1, red);
+        }
     }
     // thread 0 wrote the records (item_record) and reads them back here
     if (threadIdx.x == 0) {
@@ -732,7 +735,10 @@ __global__ __launch_bounds__(256) void k_fused_record(ReplicaDev<R>* __restrict_
     const ReplicaDev<R>& r = reps[blockIdx.x];
     if (r.nsteps <= 0 || !(r.flags & which) || !(r.flags & kRecord))
         return;   // uniform over the block
-    item_record<R, 256>(r, 0, slot, red);
+    if (which == kBrick)
+        item_record<R, 256, false>(r, 0, slot, red);
+    else
+        item_record<R, 256, true>(r, 0, slot, red);
 }
 
 // The measuring launch always records; a step launch records unless no

@@ -123,6 +123,12 @@ int brick_resident_blocks(int device, int kind);
 // Site tables of a kind's brick, and the brick's cells per axis.
 std::vector<uint32_t> brick_table(int kind);
 void brick_cells(int kind, int cells[3]);
+// LDS box of a kind's brick: cells per row and column, cells in all (basis
+// site b of a cell sits b * volume further), and link words per class.
+struct BrickBox {
+    int sx = 0, sy = 0, volume = 0, words = 0;
+};
+BrickBox brick_box(int kind);
 
 // LDS planes of the fused step for a thread region of px x py cells (tile
 // plus ring) with nb sites per cell: the region and one more ring.  FP32:

@@ -165,6 +165,11 @@ __host__ __device__ constexpr int kind_basis(int kind)
     return kind == kKindSc6 ? 1 : (kind == kKindBcc8 || kind == kKindBcc14) ? 2 : 0;
 }
 
+// Class of cell u of an axis of n cells: 0 first, 1 inner, 2 last.
+__host__ __device__ constexpr int edge_class(int u, int n) { return u == 0 ? 0 : u == n - 1 ? 2 : 1; }
+// Brick step: pairs of links a site of `kind` has.
+__host__ __device__ constexpr int brick_pairs(int kind) { return kind == kKindSc6 ? 3 : kind == kKindBcc8 ? 4 : 7; }
+
 // Whether basis site b of `kind` has the link (dz, dy, dx, bp); its type
 // slot goes to *slot.  Enumerating dz, dy, dx, bp in increasing order
 // lists the links in the canonical order the fused step sums them in.
@@ -282,6 +287,11 @@ struct ReplicaDev {
     int32_t f_kind;                 // FusedKind of the lattice
     int32_t f_pad;
     R f_kj[2];                      // J / mu_ref of the kind's type slots
+    // brick step (kBrick): links of each of the nb x 27 site classes, two per
+    // word: slot offset << 2 | code (J slot 0 or 1; 2: padding); brick_pairs
+    // words of near links, then as many of far ones, to whole 16 bytes
+    const uint32_t* b_links;
+    int32_t b_near, b_far;          // pairs in use, the most over the classes
 };
 
 struct WorkItem {

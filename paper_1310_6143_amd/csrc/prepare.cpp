@@ -1,4 +1,5 @@
 // Host-side validation and layout conversion (see prepare.hpp).
+#include "kernels.hpp"
 #include "prepare.hpp"
 
 #include <algorithm>
@@ -293,6 +294,108 @@ static void for_each_link(const HostStructure& s, int64_t i, F&& fn)
     }
 }
 
+// Link words of the brick step's site classes (see HostStructure): the row
+// of a class is that of its sites (their stencil pattern, or the SELL rows
+// one by one), near links first, each link as the cell offset its class gives
+// the column.
+static void brick_tables(HostStructure& s)
+{
+    s.brick_words.clear();
+    s.brick_near = s.brick_far = 0;
+    const HostLattice& L = s.lat;
+    if (!L.fusable || L.kind == kKindGeneric || s.wide || s.n > kBrickMaxSites || L.nx < kBrickMinEdge ||
+        L.ny < kBrickMinEdge || (L.per[2] && L.nz < kBrickMinEdge))
+        return;
+    const int classes = 27 * L.nb, pairs = brick_pairs(L.kind);
+    const BrickBox box = brick_box(L.kind);
+    struct Link {
+        int64_t off;
+        int type, part;   // part 0 near, 1 far
+        bool operator==(const Link& o) const { return off == o.off && type == o.type && part == o.part; }
+    };
+    auto row_of = [&](int64_t i, std::vector<Link>& row) {
+        row.clear();
+        if (s.stencil) {
+            const int p = s.pat_id[(size_t)i];
+            for (int k = s.pat_start[(size_t)p]; k < s.pat_start[(size_t)p + 1]; ++k)
+                if (s.pat_tab[(size_t)k] >> 4)   // offset 0: padding of the far part
+                    row.push_back({s.pat_tab[(size_t)k] >> 4, s.pat_tab[(size_t)k] & 15,
+                                   k < s.pat_far[(size_t)p] ? 0 : 1});
+            return;
+        }
+        const int d = (int)(s.deg[(size_t)i] & 0xFFFFu), near = (int)(s.deg[(size_t)i] >> 16);
+        const int64_t base = s.slice_off[(size_t)(i / kSlice)] + i % kSlice;
+        for (int k = 0; k < d; ++k) {
+            const uint32_t e = s.nb[(size_t)(base + (int64_t)k * kSlice)];
+            row.push_back({(int64_t)(e & kColMask) - i, (int)(e >> kColBits), k < near ? 0 : 1});
+        }
+    };
+    std::vector<int64_t> site((size_t)classes, -1);   // the class's first site
+    std::vector<std::vector<Link>> rows((size_t)classes);
+    std::vector<Link> row;
+    int64_t i = 0;
+    for (int z = 0; z < L.nz; ++z)
+        for (int y = 0; y < L.ny; ++y) {
+            const int czy = edge_class(z, L.nz) * 9 + edge_class(y, L.ny) * 3;
+            for (int x = 0; x < L.nx; ++x)
+                for (int b = 0; b < L.nb; ++b, ++i) {
+                    const size_t c = (size_t)(b * 27 + czy + edge_class(x, L.nx));
+                    if (site[c] < 0) {
+                        site[c] = i;
+                        row_of(i, rows[c]);
+                    } else if (s.stencil) {
+                        if (s.pat_id[(size_t)i] != s.pat_id[(size_t)site[c]])
+                            return;   // the class's rows differ (their order, say)
+                    } else {
+                        row_of(i, row);
+                        if (row != rows[c])
+                            return;
+                    }
+                }
+        }
+    std::vector<uint32_t> words((size_t)classes * box.words, 0x00020002u);   // padding: offset 0, code 2
+    int most[2] = {0, 0};
+    const int dim[3] = {L.nx, L.ny, L.nz};
+    for (int c = 0; c < classes; ++c) {
+        int used[2] = {0, 0};
+        for (const Link& link : rows[(size_t)c]) {
+            const int type = link.type, part = link.part;
+            const int64_t from[2] = {site[(size_t)c], site[(size_t)c] + link.off};
+            int d[3], b[2];
+            int64_t q[2][3];
+            for (int e = 0; e < 2; ++e) {
+                b[e] = (int)(from[e] % L.nb);
+                const int64_t cell = from[e] / L.nb;
+                q[e][0] = cell % L.nx;
+                q[e][1] = cell / L.nx % L.ny;
+                q[e][2] = cell / ((int64_t)L.nx * L.ny);
+            }
+            for (int a = 0; a < 3; ++a) {
+                d[a] = (int)(q[1][a] - q[0][a]);
+                if (d[a] > 1)
+                    d[a] -= dim[a];
+                if (d[a] < -1)
+                    d[a] += dim[a];
+            }
+            int slot = 0;
+            if (used[part] >= 2 * pairs || !kind_link(L.kind, b[0], d[2], d[1], d[0], b[1], &slot) ||
+                (type != L.slot_type[0] && type != L.slot_type[1]))
+                return;
+            const int offset = (b[1] - b[0]) * box.volume + (d[2] * box.sy + d[1]) * box.sx + d[0];
+            const uint32_t half = (uint32_t)(offset * 4 + (type == L.slot_type[0] ? 0 : 1)) & 0xFFFFu;
+            uint32_t& w = words[(size_t)c * box.words + part * pairs + used[part] / 2];
+            const int shift = used[part] % 2 ? 16 : 0;
+            w = (w & ~(0xFFFFu << shift)) | half << shift;
+            ++used[part];
+        }
+        for (int part = 0; part < 2; ++part)
+            most[part] = std::max(most[part], (used[part] + 1) / 2);
+    }
+    s.brick_words = std::move(words);
+    s.brick_near = most[0];
+    s.brick_far = most[1];
+}
+
 void set_lattice(HostStructure& s, int nb, const int cells[3], const int periodic[3])
 {
     if (!cells || !periodic)
@@ -457,6 +560,7 @@ void set_lattice(HostStructure& s, int nb, const int cells[3], const int periodi
     if (!by_basis)
         L.plane_pat = std::move(plane);
     s.lat = std::move(L);
+    brick_tables(s);
 }
 
 void set_exchange_tensors(HostStructure& s, const double* Jt, int n_types)
@@ -812,6 +916,8 @@ void fill_parameters(ReplicaDev<R>& rec, const HostStructure& s, const HostMater
     rec.f_pad = 0;
     for (int q = 0; q < 2; ++q)
         rec.f_kj[q] = L.on ? rec.jt[L.slot_type[q]] : (R)0;
+    rec.b_near = s.brick_near;
+    rec.b_far = s.brick_far;
     int32_t nent = 0;
     for (const auto& p : s.lat.pats)
         nent += (int32_t)p.size();

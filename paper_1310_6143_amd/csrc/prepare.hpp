@@ -145,15 +145,22 @@ struct HostStructure {
     std::vector<int64_t> colour_start;   // [n_colours + 1]
     // lattice declaration and fused-step patterns (set_lattice)
     HostLattice lat;
+    // brick step: link words per site class (ReplicaDev::b_links) and the
+    // pairs in use; empty when the lattice or its rows do not allow it
+    std::vector<uint32_t> brick_words;
+    int brick_near = 0, brick_far = 0;
 };
 
-// Whether the brick step is built for lattice L of n sites in a precision
-// (bytes per real): a compiled kind with at least kBrickMinEdge cells per
-// periodic axis whose spins have 31-bit byte offsets.
-inline bool brick_lattice_ok(const HostLattice& L, int64_t n, size_t real_bytes)
+// Largest lattice the brick tables are made for (sites); from kFusedMinSpins
+// on the fused step is the default.
+constexpr int64_t kBrickMaxSites = int64_t(1) << 20;
+
+// Whether the brick step can run on the structure in a precision (bytes per
+// real).  Its tables (set_lattice) exist for a compiled kind with at least kBrickMinEdge cells per periodic axis in which every
+// site of a class lists its links in the same order.
+inline bool brick_ok(const HostStructure& s, size_t real_bytes)
 {
-    return L.on && L.fusable && L.kind != kKindGeneric && L.nx >= kBrickMinEdge && L.ny >= kBrickMinEdge &&
-           (!L.per[2] || L.nz >= kBrickMinEdge) && n * 3 * (int64_t)real_bytes + 16 <= 0x7FFFFFFF;
+    return !s.brick_words.empty() && s.n * 3 * (int64_t)real_bytes + 16 <= 0x7FFFFFFF;
 }
 
 // Declares the structure's sites as a lattice of nb sites per cell on

@@ -1,7 +1,7 @@
-// Per-site pieces of the single-launch steps (fused.hip, brick.hip): the
-// record terms, the record of a replica from its work items' sums, and the
-// predictor and corrector of one site of a uniform material with scalar
-// exchange.
+// Pieces the single-launch steps (fused.hip, brick.hip) share: the record of
+// a replica from its work items' sums, and, for the plane march, the record
+// terms, predictor and corrector of one site of a uniform material with
+// scalar exchange.
 #pragma once
 
 #include "device_common.hpp"
@@ -32,8 +32,9 @@ __device__ __forceinline__ void sum4_256(const double v[4], double out[4], doubl
 
 // Record `slot` of replica r from its items' sums of parity `par`: thread t
 // < 256 adds items t, t + 256, ... in order, then the fixed 256-lane sum.
-// The same order whichever kernel runs it.
-template <typename R, int BT>
+// The same order whichever kernel runs it.  ZEEMAN: the items' energies leave
+// the applied field out (record_terms), and it is added here.
+template <typename R, int BT, bool ZEEMAN>
 __device__ void item_record(const ReplicaDev<R>& r, int par, int64_t slot, double (*red)[BT / 64])
 {
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -55,7 +56,7 @@ __device__ void item_record(const ReplicaDev<R>& r, int par, int64_t slot, doubl
         // the Zeeman part from the summed spins: S.H_app summed over the
         // sites is H_app.(sum of S)
         const double zee = (double)r.H[0] * tot[0] + (double)r.H[1] * tot[1] + (double)r.H[2] * tot[2];
-        out[3] = -r.mu_ref * (tot[3] + zee);
+        out[3] = -r.mu_ref * (ZEEMAN ? tot[3] + zee : tot[3]);
     }
 }
 

@@ -56,9 +56,14 @@ def test_brick_step_matches_oracle(kind, dims):
             assert max_angle(S, S_ref) < bound
             assert np.abs(np.concatenate([m1, m2]) - m_ref).max() < bound
             assert (np.abs(np.concatenate([E1, E2]) - E_ref) / np.abs(E_ref)).max() < bound
-            g.set_option("fused", 0)       # the two-launch step goes on from the same state
+        # the two-launch step: the same bits, records summed in another order
+        with sl.from_workload(w, precision=prec) as g:
+            g.set_option("fused", 0)
             assert g.get_option("brick_active") == 0
-            g.integrate(1)
+            m, E = g.integrate(40)
+            assert np.array_equal(S, g.get_spins())
+            assert np.abs(np.concatenate([m1, m2]) - m).max() < 1e-13
+            assert (np.abs(np.concatenate([E1, E2]) - E) / np.abs(E)).max() < 1e-12
 
 
 def test_brick_needs_five_cells_on_periodic_axes():
