@@ -185,17 +185,24 @@ inline int64_t fused_items(const HostLattice& L, const FusedShape& f)
 }
 
 // Candidate shapes for a lattice (the autotuner times them; the first is
-// the model's choice).  resident(f) gives the workgroups the device holds
-// at once for shape f.  FP32: the planes per item are chosen so that the
-// items fill whole rounds of the resident workgroups; the model counts
-// wave-instructions of one item (predictor on planes + 2 on every wave,
-// corrector on planes on the waves that hold tile cells, plane copies on
-// planes + 4) times rounds.  FP64 (the predictor's FP64 noise dominates,
-// and a partly idle last round costs little): an item's predictor planes
-// plus a fifth of its corrector planes (per wave) times the items per
-// resident workgroup, at least one.
+// the model's choice, which runs without tuning).  resident(f) gives the
+// workgroups the device (cus compute units) holds at once for shape f.  A
+// compute unit works through ceil(items / cus) items.  FP64: the predictor's
+// noise keeps the vector units busy whatever else is resident, so an item
+// costs its waves (in whole rounds of the four SIMDs) times (planes + 2
+// predictor planes) and a fifth of its corrector planes; the units' whole
+// items decide, not the rounds of the
+// resident workgroups (measured on 90 shapes of bcc blocks of 1.1M to 8.2M
+// spins: within 8% of that law; counting fractions of a round, as before,
+// took 23 x 18 x 32 planes for the 8.2M spins, 438 us a step against 275 of
+// 20 x 20 x 40, and 231 against 157 us for 4.2M).  FP32: every plane costs a
+// round of resident workgroups its barriers and copies (as much as five
+// waves), and each wave its predictor, plane copies and, where it holds
+// tile cells, corrector (4.2M spins 69.7 -> 69.2 us untuned, 1.77M 50.5 ->
+// 43.4, 8.2M 122.7 -> 112.7).  Tiles longer in y than in x run up to a tenth
+// slower in either precision (shorter runs of sites per row copied).
 template <typename Resident>
-inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds_limit, size_t real_bytes,
+inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds_limit, size_t real_bytes, int cus,
                                                 Resident&& resident, int max_count)
 {
     struct Scored {
@@ -212,9 +219,9 @@ inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds
                 const int tx = px - 2, ty = py - 2;
                 if (tx > L.nx + 6 || ty > L.ny + 6)   // far wider than the lattice
                     continue;
-                // FP64: of the tiles that give the same number of columns,
-                // only the smallest (the least ring work)
-                if (real_bytes == 8 && ((tx > kFusedMinEdge - 2 && (L.nx + tx - 2) / (tx - 1) == (L.nx + tx - 1) / tx) ||
+                // of the tiles that give the same number of columns, only
+                // the smallest (the least ring work)
+                if (((tx > kFusedMinEdge - 2 && (L.nx + tx - 2) / (tx - 1) == (L.nx + tx - 1) / tx) ||
                                         (ty > kFusedMinEdge - 2 && (L.ny + ty - 2) / (ty - 1) == (L.ny + ty - 1) / ty)))
                     continue;
                 const int R = std::max(resident(f), 1);
@@ -230,14 +237,20 @@ inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds
                         continue;   // the same planes as fewer segments
                     const int64_t items = cols * ((L.nz + planes - 1) / planes);
                     f.planes = planes;
+                    const double per_cu = (double)((items + cus - 1) / cus);
+                    const double narrow = ty > tx ? 1.08 : 1.0;
                     if (real_bytes == 8) {
-                        const double item = (planes + 2) + (double)tile_waves / waves * planes * 0.2;
-                        all.push_back({std::max((double)items / R, 1.0) * item, f});
+                        // waves per SIMD: a part round counts as a whole
+                        // one, and one wave alone takes 3/4 of what two do
+                        const int simd = (waves + 3) / 4;
+                        const bool lone = simd * std::min<int64_t>(std::max(R / cus, 1), (int64_t)per_cu) == 1;
+                        const double item = 4.0 * simd * (lone ? 1.5 : 1.0) * (planes + 2) + 0.2 * tile_waves * planes;
+                        all.push_back({per_cu * item * narrow, f});
                         continue;
                     }
                     const double item = waves * ((planes + 2) * 1.0 + (planes + 4) * 0.25) + tile_waves * planes * 0.4;
                     const double rounds = std::ceil((double)items / R);
-                    all.push_back({rounds * item * R, f});
+                    all.push_back({(rounds * 8.0 * (planes + 3) + per_cu * item) * narrow, f});
                 }
             }
     }
@@ -653,7 +666,7 @@ public:
             r.flags = 0;
             fill_parameters(r, s, m, d);
             if (sl.lat.on)
-                sl.fshape = fused_candidates(sl.lat, lds_limit(), sizeof(R),
+                sl.fshape = fused_candidates(sl.lat, lds_limit(), sizeof(R), compute_units(),
                                              [&](const FusedShape& f) { return fused_resident(sl.lat, f); }, 1)
                                 .at(0);
             upload_materials(q, m, d);
@@ -810,17 +823,24 @@ public:
         auto it = fused_occ_.find(key);
         if (it == fused_occ_.end())
             it = fused_occ_.emplace(key, fused_resident_blocks<R>(device_, L.kind, L.nb, f.bt, 16)).first;
-        int cus = 0, lds_cu = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device_) != hipSuccess || cus <= 0)
-            cus = 256;
-        if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device_) != hipSuccess ||
-            lds_cu <= 0)
-            lds_cu = 160 * 1024;
+        const int cus = compute_units();
+        if (lds_cu_ == 0 && (hipDeviceGetAttribute(&lds_cu_, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
+                                                   device_) != hipSuccess ||
+                             lds_cu_ <= 0))
+            lds_cu_ = 160 * 1024;
+        const int lds_cu = lds_cu_;
         const size_t per_wg =
             fused_lds_bytes(L.kind, fused_plane_bytes(f, L.nb, sizeof(R)), f.bt) + fused_static_lds(f.bt, sizeof(R));
         const int by_lds = (int)std::max<size_t>(1, (size_t)lds_cu / per_wg);
         const int by_regs = std::max(1, it->second / cus);
         return cus * std::min(by_lds, by_regs);
+    }
+    int compute_units()
+    {
+        if (cus_ == 0 &&
+            (hipDeviceGetAttribute(&cus_, hipDeviceAttributeMultiprocessorCount, device_) != hipSuccess || cus_ <= 0))
+            cus_ = 256;
+        return cus_;
     }
     size_t lds_limit()
     {
@@ -831,8 +851,8 @@ public:
     std::vector<FusedShape> fused_candidate_shapes(int q, int max_count)
     {
         const HostLattice& L = slots_[q].lat;
-        return fused_candidates(L, lds_limit(), sizeof(R), [&](const FusedShape& f) { return fused_resident(L, f); },
-                                max_count);
+        return fused_candidates(L, lds_limit(), sizeof(R), compute_units(),
+                                [&](const FusedShape& f) { return fused_resident(L, f); }, max_count);
     }
 
     // Write the current state (spins are normalised doubles, 3n).
@@ -1543,6 +1563,7 @@ private:
     int fgrid_ = 0;
     std::map<int, int> fused_occ_;    // register-limited resident workgroups per (kind, nb, bt)
     size_t lds_limit_ = 0;
+    int cus_ = 0, lds_cu_ = 0;        // device limits, queried once
     std::vector<FusedItem> fwork_;
     FusedItem* d_fwork_ = nullptr;    // items, then their count (int) at fwork_cap_
     int64_t fwork_cap_ = 0;
