@@ -301,8 +301,10 @@ bool fused_wanted(const sllg_system* s)
 // 35.6 at 1,024,000; FP64 7.3 and 16.0, 55.3 and 69.3).
 bool brick_wanted(const sllg_system* s)
 {
-    if (s->opt_fused != 1 || fused_wanted(s))
+    if (s->opt_fused != 1 || (fused_wanted(s) && !s->st.far.on))
         return false;
+    if (s->st.far.on)
+        return true;   // the long-range step, at any size
     return s->st.lat.kind != kKindBcc14 || s->n <= (s->prec == SLLG_FP32 ? 150000 : 100000);
 }
 
@@ -886,6 +888,7 @@ sllg_status sllg_set_neighbours(sllg_system* sys, const int64_t* row_ptr, const 
     return guard(sys, [&] {
         HostStructure st = build_structure(sys->n, row_ptr, col, ntype, J, n_types,
                                            sys->opt_check_symmetry != 0, kHaloCap, sys->opt_stencil != 0);
+        detect_long(st);
         st.tile_request = (int)sys->opt_tile_sites;
         build_colours(st, false);   // no lattice declared yet
         drop_engine(sys);

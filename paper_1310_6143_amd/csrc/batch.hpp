@@ -268,11 +268,20 @@ inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds
     return out;
 }
 
-// Bricks of a lattice (brick step).
+// Cells per axis of a brick (brick step) or tile (long-range step).
+inline void item_cells(int kind, int c[3])
+{
+    if (kind == kKindLong)
+        long_cells(c);
+    else
+        brick_cells(kind, c);
+}
+
+// Bricks or tiles of a lattice.
 inline int64_t brick_items(const HostLattice& L)
 {
     int c[3];
-    brick_cells(L.kind, c);
+    item_cells(L.kind, c);
     return (int64_t)((L.nx + c[0] - 1) / c[0]) * ((L.ny + c[1] - 1) / c[1]) * ((L.nz + c[2] - 1) / c[2]);
 }
 
@@ -309,7 +318,10 @@ inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size
         b += r(ent * sizeof(FusedEntry)) + r(s.lat.pats.size() * 16) + r(s.lat.plane_pat.size()) +
              r((size_t)fused_item_cap(s.lat) * 64);
     } else if (plain_interactions(s, m) && brick_ok(s, real_bytes)) {
-        b += r((size_t)brick_items(s.lat) * 64) + r(s.brick_words.size() * 4);
+        b += r((size_t)brick_items(s.far.on ? s.far : s.lat) * 64) + r(s.brick_words.size() * 4) +
+             (s.far.on ? r((kLongHead + 2 * s.columns.size()) * 4) +
+                             r(s.columns.size() * (2 * kLongReach + 1) * real_bytes)
+                       : 0);
     }
     b += r(m.mat_mu.size() * sizeof(MaterialDev<double>));
     const size_t groups = (blocks + kGroupTiles - 1) / kGroupTiles;
@@ -397,6 +409,7 @@ public:
         // bricks in site order and then its record item
         int b_kind = 0;
         std::vector<FusedItem> b_items;
+        std::vector<HostStructure::LongColumn> columns;   // long-range step
     };
 
     Batch(int device, Allocator* alloc, int max_replicas)
@@ -618,15 +631,17 @@ public:
                 r.dm_part = dpart;
             }
             r.b_links = nullptr;
+            r.l_head = nullptr;
+            r.l_J = nullptr;
             r.f_ent = nullptr;
             r.f_pat = nullptr;
             r.f_plane = nullptr;
             r.f_partials = nullptr;
             r.f_px = r.f_py = r.f_items = 0;
             if (plain_interactions(s, m) && brick_ok(s, sizeof(R))) {
-                const HostLattice* L = &s.lat;
+                const HostLattice* L = s.far.on ? &s.far : &s.lat;
                 int c[3];
-                brick_cells(L->kind, c);
+                item_cells(L->kind, c);
                 sl.b_kind = L->kind;
                 int32_t idx = 0;
                 for (int z0 = 0; z0 < L->nz; z0 += c[2])
@@ -635,10 +650,16 @@ public:
                             sl.b_items.push_back(FusedItem{q, x0, y0, z0, z0 + c[2], idx++});
                 sl.f_cap_items = idx;
                 sl.b_items.push_back(FusedItem{q, 0, 0, 0, -1, -1});
-                uint32_t* words = (uint32_t*)get(s.brick_words.size() * 4);
-                hip_check(hipMemcpy(words, s.brick_words.data(), s.brick_words.size() * 4, hipMemcpyHostToDevice),
-                          "upload brick links");
-                r.b_links = words;
+                if (s.far.on) {
+                    sl.columns = s.columns;
+                    r.l_head = (const int32_t*)get((kLongHead + 2 * s.columns.size()) * 4);
+                    r.l_J = (const R*)get(s.columns.size() * (2 * kLongReach + 1) * sizeof(R));
+                } else {
+                    uint32_t* words = (uint32_t*)get(s.brick_words.size() * 4);
+                    hip_check(hipMemcpy(words, s.brick_words.data(), s.brick_words.size() * 4, hipMemcpyHostToDevice),
+                              "upload brick links");
+                    r.b_links = words;
+                }
             }
             if (fused_precision_ok(s.lat, s.n, sizeof(R))) {
                 size_t ent = 0;
@@ -727,6 +748,43 @@ public:
                             hipMemcpyHostToDevice),
                   "upload materials");
         upload_fused(q);
+        upload_long(q);
+    }
+
+    // Long-range step: the columns of links dealt to the four waves, longest
+    // first, each to the wave with the fewest spins to read, and their
+    // couplings (J / mu_ref from the replica's table).
+    void upload_long(int q)
+    {
+        const Slot& sl = slots_[q];
+        const ReplicaDev<R>& r = sl.rec;
+        if (!r.l_head)
+            return;
+        std::vector<HostStructure::LongColumn> cols = sl.columns;
+        std::stable_sort(cols.begin(), cols.end(), [](const auto& a, const auto& b) { return a.reach > b.reach; });
+        std::vector<const HostStructure::LongColumn*> of[4];
+        int load[4] = {0, 0, 0, 0};
+        for (const auto& c : cols) {
+            const int w = (int)(std::min_element(load, load + 4) - load);
+            of[w].push_back(&c);
+            load[w] += 2 * c.reach + 5;
+        }
+        std::vector<int32_t> head(kLongHead, 0);
+        std::vector<R> J;
+        for (int w = 0; w < 4; ++w) {
+            head[(size_t)w + 1] = head[(size_t)w] + (int32_t)of[w].size();
+            for (const auto* c : of[w]) {
+                head.push_back(long_slot_offset(c->dx, c->dy));
+                head.push_back(c->reach);
+                for (int k = 0; k <= 2 * kLongReach; ++k) {   // from -reach; unused ones past 2 reach + 1
+                    const int dz = k + kLongReach - c->reach;
+                    const int t = dz <= 2 * kLongReach ? c->type[dz] : -1;
+                    J.push_back(t >= 0 ? r.jt[t] : (R)0);
+                }
+            }
+        }
+        hip_check(hipMemcpy((void*)r.l_head, head.data(), head.size() * 4, hipMemcpyHostToDevice), "upload columns");
+        hip_check(hipMemcpy((void*)r.l_J, J.data(), J.size() * sizeof(R), hipMemcpyHostToDevice), "upload columns");
     }
 
     // Fused step: pattern entries for the slot's shape (LDS offsets depend
@@ -1098,7 +1156,9 @@ public:
                     if (sl.used && sl.rec.nsteps > 0 && sl.b_kind == kind)
                         all.insert(all.end(), sl.b_items.begin(), sl.b_items.end());
             const int n = (int)all.size();
-            if (n > 0 && !b.table) {
+            if (n > 0 && kind == kKindLong) {
+                b.resident = std::max(long_resident_blocks<R>(device_) & ~7, 8);
+            } else if (n > 0 && !b.table) {
                 const std::vector<uint32_t> tab = brick_table(kind);
                 if (tab.empty())
                     fail(SLLG_E_STATE, "brick table does not fit its workgroup");
@@ -1434,7 +1494,9 @@ private:
         hipError_t e = hipSuccess;
         for (int kind = 1; kind < kBrickKinds && e == hipSuccess; ++kind) {
             const BrickList& b = brick_[kind];
-            if (b.grid > 0)
+            if (b.grid > 0 && kind == kKindLong)
+                e = launch_long<R>(d_reps_, b.d, b.count(), b.grid, k, remap_, measure, st);
+            else if (b.grid > 0)
                 e = launch_brick<R>(d_reps_, b.d, b.count(), b.table, b.grid, k, remap_, measure, kind, st);
         }
         return e;
@@ -1569,7 +1631,7 @@ private:
     int64_t fwork_cap_ = 0;
 
     // brick step: items and their count per kind, and the kind's site tables
-    static constexpr int kBrickKinds = kKindBcc14 + 1;
+    static constexpr int kBrickKinds = kKindLong + 1;
     struct BrickList {
         FusedItem* d = nullptr;   // [cap] items, then their count
         int64_t cap = 0;

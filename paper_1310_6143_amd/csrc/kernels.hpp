@@ -130,6 +130,17 @@ struct BrickBox {
 };
 BrickBox brick_box(int kind);
 
+// Long-range step (longrange.hip) of step k over the listed tiles: the
+// predictor and corrector launches, or with measure the m and E sums.
+template <typename R>
+hipError_t launch_long(const ReplicaDev<R>* reps, const FusedItem* items, const int* n_items, int grid, int k,
+                       int remap, bool measure, hipStream_t st);
+template <typename R>
+int long_resident_blocks(int device);
+// Slot offset of a column of links, and the tile's cells per axis.
+int long_slot_offset(int dx, int dy);
+void long_cells(int cells[3]);
+
 // LDS planes of the fused step for a thread region of px x py cells (tile
 // plus ring) with nb sites per cell: the region and one more ring.  FP32:
 // 16 bytes per site (x, y, z, an unused word), sites basis-major, row after

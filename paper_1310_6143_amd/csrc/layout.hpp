@@ -158,7 +158,11 @@ constexpr int kBrickMinEdge = 5;
 // is (dz, dy, dx, bp): the neighbour is basis site bp of the cell offset by
 // (dx, dy, dz).  Kind 0 is any other lattice the fused step takes, its
 // links read from a table at run time.
-enum FusedKind : int32_t { kKindGeneric = 0, kKindSc6 = 1, kKindBcc8 = 2, kKindBcc14 = 3 };
+// kKindLong: simple cubic with one set of links up to kLongReach cells away
+// (the long-range step alone, longrange.hip).
+enum FusedKind : int32_t { kKindGeneric = 0, kKindSc6 = 1, kKindBcc8 = 2, kKindBcc14 = 3, kKindLong = 4 };
+constexpr int kLongReach = 4;
+constexpr int kLongHead = 8;   // words before the column list: first column of each of the four waves, their end
 
 __host__ __device__ constexpr int kind_basis(int kind)
 {
@@ -292,6 +296,10 @@ struct ReplicaDev {
     // words of near links, then as many of far ones, to whole 16 bytes
     const uint32_t* b_links;
     int32_t b_near, b_far;          // pairs in use, the most over the classes
+    // long-range step: [kLongHead] column ranges of the four waves, then
+    // (slot offset, reach) of each column; [columns][2 kLongReach + 1] J / mu_ref
+    const int32_t* l_head;
+    const R* l_J;
 };
 
 struct WorkItem {

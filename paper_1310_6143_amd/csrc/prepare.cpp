@@ -560,7 +560,122 @@ void set_lattice(HostStructure& s, int nb, const int cells[3], const int periodi
     if (!by_basis)
         L.plane_pat = std::move(plane);
     s.lat = std::move(L);
+    s.far = HostLattice{};   // a declared lattice has no links beyond the next cell
+    s.columns.clear();
     brick_tables(s);
+}
+
+void detect_long(HostStructure& s)
+{
+    s.far = HostLattice{};
+    s.columns.clear();
+    constexpr int H = kLongReach, kEdge = 2 * H + 1;
+    if (!s.wide || s.n > 0x7FFFFFFF / 3)
+        return;
+    const size_t np = s.w_near.size();
+    auto row_of = [&](size_t p) {
+        std::vector<std::pair<int64_t, int>> row;   // (offset, type)
+        for (int e = 0; e < s.w_len; ++e) {
+            const int32_t raw = s.w_tab[(size_t)e * np + p];
+            if ((raw & 31) != kMaxTypes)
+                row.emplace_back(raw >> 5, raw & 31);
+        }
+        return row;
+    };
+    // every factorisation of n into edges is tried; whichever passes the full
+    // check is a valid reading of the rows
+    int64_t nx = 0, ny = 0, nz = 0;
+    // the links of site i as cell offsets; false when one reaches too far
+    auto links_of = [&](int64_t i, std::vector<int>& set) {   // [kEdge^3] type by offset, -1 none
+        set.assign(kEdge * kEdge * kEdge, -1);
+        const int64_t at[3] = {i % nx, i / nx % ny, i / (nx * ny)}, dim[3] = {nx, ny, nz};
+        for (const auto& l : row_of(s.w_pid[(size_t)i])) {
+            const int64_t j = i + l.first;
+            if (j < 0 || j >= s.n)
+                return false;
+            const int64_t to[3] = {j % nx, j / nx % ny, j / (nx * ny)};
+            int64_t d[3];
+            for (int a = 0; a < 3; ++a) {
+                d[a] = to[a] - at[a];
+                if (d[a] > H)
+                    d[a] -= dim[a];
+                if (d[a] < -H)
+                    d[a] += dim[a];
+                if (d[a] < -H || d[a] > H)
+                    return false;
+            }
+            int& t = set[(size_t)(((d[2] + H) * kEdge + d[1] + H) * kEdge + d[0] + H)];
+            if (t >= 0 || (d[0] == 0 && d[1] == 0 && d[2] == 0))
+                return false;
+            t = l.second;
+        }
+        return true;
+    };
+    // a row depends on the distance to the lattice's edges, up to H cells: one
+    // pattern and one check per such class of sites
+    auto cls = [](int64_t u, int64_t n) { return u < H ? u : u >= n - H ? u - n + 2 * H + 1 : (int64_t)H; };
+    std::vector<int> pat, links, set;
+    auto fits = [&] {
+        if (!links_of(0, links) || !links_of(s.n / 2, set) || set != links)
+            return false;
+        pat.assign((size_t)(kEdge * kEdge * kEdge), -1);
+        for (int64_t z = 0, i = 0; z < nz; ++z)
+            for (int64_t y = 0; y < ny; ++y) {
+                const int64_t c = (cls(z, nz) * kEdge + cls(y, ny)) * kEdge;
+                for (int64_t x = 0; x < nx; ++x, ++i) {
+                    int& p = pat[(size_t)(c + cls(x, nx))];
+                    if (p < 0) {
+                        if (!links_of(i, set) || set != links)
+                            return false;
+                        p = s.w_pid[(size_t)i];
+                    } else if (p != s.w_pid[(size_t)i]) {
+                        return false;
+                    }
+                }
+            }
+        return true;
+    };
+    bool found = false;
+    for (nx = kEdge; !found && nx * kEdge * kEdge <= s.n; ++nx) {
+        if (s.n % nx)
+            continue;
+        for (ny = kEdge; nx * ny * kEdge <= s.n; ++ny)
+            if (s.n / nx % ny == 0) {
+                nz = s.n / (nx * ny);
+                if ((found = nx <= 0xFFFF && ny <= 0xFFFF && nz <= 0xFFFF && fits()))
+                    break;
+            }
+        if (found)
+            break;
+    }
+    if (!found)
+        return;
+    for (int dy = -H; dy <= H; ++dy)
+        for (int dx = -H; dx <= H; ++dx) {
+            HostStructure::LongColumn col;
+            col.dx = dx;
+            col.dy = dy;
+            bool any = false;
+            for (int dz = -H; dz <= H; ++dz) {
+                const int t = links[(size_t)(((dz + H) * kEdge + dy + H) * kEdge + dx + H)];
+                col.type[dz + H] = t;
+                if (t >= 0) {
+                    any = true;
+                    col.reach = std::max(col.reach, std::abs(dz));
+                }
+            }
+            if (any)
+                s.columns.push_back(col);
+        }
+    HostLattice L;
+    L.on = true;
+    L.nb = 1;
+    L.nx = (int)nx;
+    L.ny = (int)ny;
+    L.nz = (int)nz;
+    L.per[0] = L.per[1] = L.per[2] = true;
+    L.kind = kKindLong;
+    s.far = std::move(L);
 }
 
 void set_exchange_tensors(HostStructure& s, const double* Jt, int n_types)
@@ -905,7 +1020,7 @@ void fill_parameters(ReplicaDev<R>& rec, const HostStructure& s, const HostMater
     if (fused_precision_ok(s.lat, s.n, sizeof(R)) && plain_interactions(s, m))
         flags |= kFused;
     rec.flags = flags;
-    const HostLattice& L = s.lat;
+    const HostLattice& L = s.far.on ? s.far : s.lat;   // no lattice is declared with s.far
     rec.f_nb = L.nb;
     rec.f_nx = L.nx;
     rec.f_ny = L.ny;

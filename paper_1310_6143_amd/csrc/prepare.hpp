@@ -149,7 +149,22 @@ struct HostStructure {
     // pairs in use; empty when the lattice or its rows do not allow it
     std::vector<uint32_t> brick_words;
     int brick_near = 0, brick_far = 0;
+    // long-range step: the simple-cubic lattice found in the wide form's rows
+    // (kind kKindLong) and its columns of links; off when there is none
+    HostLattice far;
+    struct LongColumn {
+        int dx = 0, dy = 0, reach = 0;
+        int type[2 * kLongReach + 1];   // by dz + kLongReach; -1: no link
+    };
+    std::vector<LongColumn> columns;
 };
+
+// Fills s.far and s.columns when the wide form's rows are those of a
+// simple-cubic lattice, site i = x + nx (y + ny z), periodic on every axis
+// with at least 2 kLongReach + 1 cells, whose sites all have the same links
+// (cell offsets and types) at most kLongReach cells away on each axis.
+// Every pattern and every site's pattern is checked.
+void detect_long(HostStructure& s);
 
 // Largest lattice the brick tables are made for (sites); from kFusedMinSpins
 // on the fused step is the default.
@@ -160,7 +175,7 @@ constexpr int64_t kBrickMaxSites = int64_t(1) << 20;
 // site of a class lists its links in the same order.
 inline bool brick_ok(const HostStructure& s, size_t real_bytes)
 {
-    return !s.brick_words.empty() && s.n * 3 * (int64_t)real_bytes + 16 <= 0x7FFFFFFF;
+    return (!s.brick_words.empty() || s.far.on) && s.n * 3 * (int64_t)real_bytes + 16 <= 0x7FFFFFFF;
 }
 
 // Declares the structure's sites as a lattice of nb sites per cell on
