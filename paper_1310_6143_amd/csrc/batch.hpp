@@ -319,7 +319,7 @@ inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size
              r((size_t)fused_item_cap(s.lat) * 64);
     } else if (plain_interactions(s, m) && brick_ok(s, real_bytes)) {
         b += r((size_t)brick_items(s.far.on ? s.far : s.lat) * 64) + r(s.brick_words.size() * 4) +
-             (s.far.on ? r((kLongHead + 2 * s.columns.size()) * 4) +
+             (s.far.on ? r((kLongHead + s.columns.size()) * 4) +
                              r(s.columns.size() * (2 * kLongReach + 1) * real_bytes)
                        : 0);
     }
@@ -633,6 +633,7 @@ public:
             r.b_links = nullptr;
             r.l_head = nullptr;
             r.l_J = nullptr;
+            r.l_columns = r.l_pad = 0;
             r.f_ent = nullptr;
             r.f_pat = nullptr;
             r.f_plane = nullptr;
@@ -652,7 +653,8 @@ public:
                 sl.b_items.push_back(FusedItem{q, 0, 0, 0, -1, -1});
                 if (s.far.on) {
                     sl.columns = s.columns;
-                    r.l_head = (const int32_t*)get((kLongHead + 2 * s.columns.size()) * 4);
+                    r.l_head = (const int32_t*)get((kLongHead + s.columns.size()) * 4);
+                    r.l_columns = (int32_t)s.columns.size();
                     r.l_J = (const R*)get(s.columns.size() * (2 * kLongReach + 1) * sizeof(R));
                 } else {
                     uint32_t* words = (uint32_t*)get(s.brick_words.size() * 4);
@@ -772,11 +774,11 @@ public:
         std::vector<int32_t> head(kLongHead, 0);
         std::vector<R> J;
         for (int w = 0; w < 4; ++w) {
-            head[(size_t)w + 1] = head[(size_t)w] + (int32_t)of[w].size();
+            head[(size_t)(8 * w)] = (int32_t)head.size() - kLongHead;
             for (const auto* c : of[w]) {
+                ++head[(size_t)(8 * w + 1 + kLongReach - c->reach)];
                 head.push_back(long_slot_offset(c->dx, c->dy));
-                head.push_back(c->reach);
-                for (int k = 0; k <= 2 * kLongReach; ++k) {   // from -reach; unused ones past 2 reach + 1
+                for (int k = 0; k <= 2 * kLongReach; ++k) {   // unused past 2 reach + 1
                     const int dz = k + kLongReach - c->reach;
                     const int t = dz <= 2 * kLongReach ? c->type[dz] : -1;
                     J.push_back(t >= 0 ? r.jt[t] : (R)0);
@@ -1070,13 +1072,21 @@ public:
         build_bricks(fused);
         // two-launch tiles of the replicas that do not take the brick step
         // (the Monte Carlo records take them in fused mode too)
+        // the reduction items first, so that they run beside the tiles
         work_.clear();
+        auto runs_tiles = [&](const Slot& sl) {
+            return sl.used && sl.rec.nsteps > 0 && (fused || !brick_on_ || !sl.b_kind);
+        };
         for (size_t q = 0; q < slots_.size(); ++q)
-                if (slots_[q].used && slots_[q].rec.nsteps > 0 && (fused || !brick_on_ || !slots_[q].b_kind))
-                    for (int32_t b : tile_order(slots_[q].rec.blocks, order_ ? slots_[q].plane_tiles : 0,
-                                                group_ > 0 ? group_
-                                                           : balanced_group(slots_[q].plane_tiles, slots_[q].rec.tile)))
-                        work_.push_back(WorkItem{(int32_t)q, b});
+            if (runs_tiles(slots_[q]))
+                for (int32_t g = 0; g * kGroupTiles < slots_[q].rec.blocks; ++g)
+                    work_.push_back(WorkItem{(int32_t)q, -1 - g});
+        for (size_t q = 0; q < slots_.size(); ++q)
+            if (runs_tiles(slots_[q]))
+                for (int32_t b : tile_order(slots_[q].rec.blocks, order_ ? slots_[q].plane_tiles : 0,
+                                            group_ > 0 ? group_
+                                                       : balanced_group(slots_[q].plane_tiles, slots_[q].rec.tile)))
+                    work_.push_back(WorkItem{(int32_t)q, b});
         fwork_.clear();
         if (fused)
             for (size_t q = 0; q < slots_.size(); ++q)

@@ -415,30 +415,53 @@ __device__ __forceinline__ MaterialDev<R> uniform_material(const ReplicaDev<R>& 
     return m;
 }
 
-// End of a chunk for one replica (one thread): the averaging block sums of
-// the chunk's records (kAverage), then the step counter, buffer parity and
-// record position advance by the chunk's steps.
+// End of a chunk for one replica: the averaging block sums of the chunk's
+// records (kAverage; the whole block calls it, 64 threads or more), then
+// (one thread) the step counter, buffer parity and record position advance
+// by the chunk's steps.  64 records are read at once into LDS and added one
+// by one in step order, a thread per column: with one thread reading and
+// adding them the last launch of a 64-step chunk took 17 us.
 template <typename R>
-__device__ inline void accumulate_records(const ReplicaDev<R>& r)
+__device__ inline void accumulate_records(const ReplicaDev<R>& r, double (*buf)[5])
 {
     if (r.nsteps <= 0 || !(r.flags & kAverage))
-        return;
-    for (int t = 0; t < r.nsteps; ++t) {
-        const int64_t sample = (int64_t)(r.step + (uint64_t)t) - r.avg_first;
-        if (sample < 0)
-            continue;
-        const int64_t b = sample / r.avg_block_len;
-        if (b >= r.avg_blocks)
-            break;
-        const double* rec = r.records + 4 * (r.rec_pos + t);
-        const double mx = rec[0], my = rec[1], mz = rec[2];
-        double* a = r.acc + 5 * b;
-        a[0] += sqrt(mx * mx + my * my + mz * mz);
-        a[1] += mx;
-        a[2] += my;
-        a[3] += mz;
-        a[4] += rec[3];
+        return;   // uniform over the block
+    const int lane = (int)threadIdx.x, n = r.nsteps;
+    const int64_t first = (int64_t)r.step - r.avg_first, len = r.avg_block_len;
+    int64_t b = -1, left = 0;   // the block the column's sum belongs to, and the samples it still takes
+    double sum = 0.0;
+    for (int t0 = 0; t0 < n; t0 += 64) {
+        if (lane < 64 && t0 + lane < n) {
+            const double* rec = r.records + 4 * (r.rec_pos + t0 + lane);
+            const double mx = rec[0], my = rec[1], mz = rec[2];
+            buf[lane][0] = sqrt(mx * mx + my * my + mz * mz);
+            buf[lane][1] = mx;
+            buf[lane][2] = my;
+            buf[lane][3] = mz;
+            buf[lane][4] = rec[3];
+        }
+        __syncthreads();
+        if (lane < 5)
+            for (int j = 0; j < 64 && t0 + j < n; ++j) {
+                const int64_t sample = first + t0 + j;
+                if (sample < 0 || b >= r.avg_blocks)
+                    continue;
+                if (left == 0) {
+                    if (b >= 0)
+                        r.acc[5 * b + lane] = sum;
+                    b = b < 0 ? sample / len : b + 1;
+                    left = (b + 1) * len - sample;
+                    if (b >= r.avg_blocks)
+                        continue;
+                    sum = r.acc[5 * b + lane];
+                }
+                sum += buf[j][lane];
+                --left;
+            }
+        __syncthreads();
     }
+    if (lane < 5 && b >= 0 && b < r.avg_blocks)
+        r.acc[5 * b + lane] = sum;
 }
 
 template <typename R>

@@ -718,11 +718,12 @@ __global__ __launch_bounds__(256) void k_fused_finish(ReplicaDev<R>* __restrict_
                 item_record<R, 256, true>(r, k & 1, k - 1, red);
         }
     }
-    // thread 0 wrote the records (item_record) and reads them back here
-    if (threadIdx.x == 0) {
-        accumulate_records(r);
+    __shared__ double buf[64][5];
+    __syncthreads();   // thread 0 wrote the records (item_record)
+    accumulate_records(r, buf);
+    __syncthreads();
+    if (threadIdx.x == 0)
         advance_replica(r);
-    }
 }
 
 // After a measuring launch of the current state (k < 0), one workgroup per

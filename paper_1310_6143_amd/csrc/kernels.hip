@@ -49,7 +49,7 @@
 #define SLLG_WAVES_F32_PS 5
 #endif
 #ifndef SLLG_WAVES_F64_PS
-#define SLLG_WAVES_F64_PS 3
+#define SLLG_WAVES_F64_PS 4
 #endif
 #ifndef SLLG_WAVES_F32_GEN
 #define SLLG_WAVES_F32_GEN 4
@@ -60,7 +60,9 @@
 // Waves per SIMD the step kernels are compiled for: as many as their LDS
 // allows (register use is capped to match).  Kernel variant V: 0 uniform
 // material, 1 per-site materials and easy axes, 2 general (also exchange
-// tensors and cubic anisotropy).
+// tensors and cubic anisotropy).  Per-site FP64: 4, so that two 8-wave
+// workgroups share a unit (196,053 ragged spins: 31.1 us a step with 3, when
+// its 383 tiles took two rounds, 25.7 with 4; 24,499 spins 18.4 and 18.8).
 #define SLLG_STEP_ATTRS                                                                        \
     __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(                       \
         sizeof(R) == 4 ? (V == 0 ? SLLG_WAVES_F32 : V == 1 ? SLLG_WAVES_F32_PS : SLLG_WAVES_F32_GEN)   \
@@ -140,45 +142,68 @@ struct TileLds {
     alignas(16) uint8_t pid[tile_sites<R>()];
 };
 
-// Caller synchronises before (tables may still be read) and after.
+// Caller synchronises before (tables may still be read) and after.  Every
+// load is issued before the first is waited for (one after another they took
+// 2400 cycles of a 14,600-cycle predictor launch on 4,096 spins); an entry's
+// coupling comes from the lane of its wave that holds it.
 template <typename R, bool TX>
 __device__ __forceinline__ void stage_tables(const ReplicaDev<R>& r, Shared<R>& sh)
 {
-    if (threadIdx.x <= kMaxTypes)
-        sh.jt[threadIdx.x] = threadIdx.x < kMaxTypes ? r.jt[threadIdx.x] : (R)0;
+    const int t = (int)threadIdx.x;
+    static_assert(kMaxTypes == 16 && kMaxPatterns < kBlockThreads && kMaxPatternEntries % kBlockThreads == 0, "");
+    const R jv = gload(r.jt, t & (kMaxTypes - 1));
     const bool tensor = TX && (r.flags & kTensor);
-    if (tensor && threadIdx.x < (kMaxTypes + 1) * 9) {
-        const int t = threadIdx.x / 9, q = threadIdx.x % 9;
-        sh.jm[t][q] = t < kMaxTypes ? r.jm[t][q] : (R)0;
+    if (t <= kMaxTypes)
+        sh.jt[t] = t < kMaxTypes ? jv : (R)0;
+    if (tensor && t < (kMaxTypes + 1) * 9) {
+        const int y = t / 9, q = t % 9;
+        sh.jm[y][q] = y < kMaxTypes ? r.jm[y][q] : (R)0;
     }
     if (r.flags & kStencil) {
-        const int np = r.n_patterns;
-        for (int q = threadIdx.x; q <= np; q += kBlockThreads)
-            sh.pat_start[q] = gload(r.pat_start, q);
-        for (int q = threadIdx.x; q < np; q += kBlockThreads)
-            sh.pat_far[q] = gload(r.pat_far, q);
-        const int ne = gload(r.pat_start, np);
-        for (int q = threadIdx.x; q < ne; q += kBlockThreads) {
-            const int32_t raw = gload(r.pat_tab, q);
-            sh.pat[q].off = (raw >> 4) * (int)(3 * sizeof(R));
-            sh.pat[q].J = (raw >> 4) != 0 ? r.jt[raw & 15] : (R)0;   // offset 0: padding
-            if (tensor)
-                sh.ptype[q] = (raw >> 4) != 0 ? (uint8_t)(raw & 15) : (uint8_t)kMaxTypes;
+        constexpr int E = kMaxPatternEntries / kBlockThreads;
+        const int np = r.n_patterns, ne = r.n_entries;
+        const uint16_t start = t <= np ? gload(r.pat_start, t) : (uint16_t)0;
+        const uint16_t far = t < np ? gload(r.pat_far, t) : (uint16_t)0;
+        int32_t raw[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+            raw[j] = t + j * kBlockThreads < ne ? gload(r.pat_tab, t + j * kBlockThreads) : 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const int q = t + j * kBlockThreads;
+            const R J = __shfl(jv, raw[j] & 15, 64);   // every lane takes part
+            if (q < ne) {
+                sh.pat[q].off = (raw[j] >> 4) * (int)(3 * sizeof(R));
+                sh.pat[q].J = (raw[j] >> 4) != 0 ? J : (R)0;   // offset 0: padding
+                if (tensor)
+                    sh.ptype[q] = (raw[j] >> 4) != 0 ? (uint8_t)(raw[j] & 15) : (uint8_t)kMaxTypes;
+            }
         }
+        if (t <= np)
+            sh.pat_start[t] = start;
+        if (t < np)
+            sh.pat_far[t] = far;
     }
 }
 
-// 16-byte chunks [skip, skip + lim) of dst come from memory at base, the
-// others are zero.
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+// 16-byte chunks [skip, skip + lim) of dst come from memory at base by direct
+// global-to-LDS loads, all in flight together (through registers each round
+// of the loop waited for its own load: three to four dependent round trips
+// before a tile began); the others are zero.  The next barrier completes it.
 __device__ __forceinline__ void stage_chunks(const void* base, int skip, int lim, int nc, v4i* dst)
 {
     const __amdgpu_buffer_rsrc_t rs = spin_rsrc(base, lim * 16);
-    for (int q = threadIdx.x; q < nc; q += kBlockThreads) {
-        const int c = q - skip;
-        v4i v = {0, 0, 0, 0};
-        if (c >= 0 && c < lim)
-            v = __builtin_amdgcn_raw_buffer_load_b128(rs, c * 16, 0, 0);
-        dst[q] = v;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+    for (int q0 = 64 * wave; q0 < nc; q0 += kBlockThreads) {   // uniform over the wave
+        const int q = q0 + lane, c = q - skip;
+        if (q < nc) {
+            if (c >= 0 && c < lim)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(dst + q0), 16, c * 16, 0, 0, 0);
+            else
+                dst[q] = v4i{0, 0, 0, 0};
+        }
     }
 }
 
@@ -418,33 +443,46 @@ __device__ __forceinline__ V3<R> exchange_sum(const ReplicaDev<R>& r, const R* _
 // ---------------------------------------------------------------------------
 constexpr int kWaves = kBlockThreads / 64;
 
-// Block-wide sum of four values in a fixed order; result valid in thread 0.
-// Ends with a barrier so `red` can be reused at once.
-__device__ __forceinline__ void block_sum4(const double v[4], double out[4], double (*red)[kWaves])
+// Scratch of block_sum4: the four row sums of every wave, by component.
+typedef double BlockSums[4][kWaves][4];
+
+// Block-wide sum of four values in a fixed order (rows of 16 lanes, the four
+// rows of a wave, the waves in turn); the sum of v[c] is valid in thread c <
+// 4.  The rows' sums meet in LDS and one lane per component adds them: with
+// the rows read lane by lane and one thread adding all four components the
+// sums took a sixth of a predictor launch on 4,096 spins.  Ends with a
+// barrier so `red` can be reused at once.
+__device__ __forceinline__ double block_sum4(const double v[4], BlockSums& red)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double rows[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double w = wave_sum(v[c]);
-        if (lane == 0)
-            red[c][wave] = w;
+    for (int c = 0; c < 4; ++c)
+        rows[c] = row_sum(v[c]);
+    if ((lane & 15) == 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            red[c][wave][lane >> 4] = rows[c];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    double s = 0.0;
+    if (threadIdx.x < 4) {
+        const double(*p)[4] = red[threadIdx.x];
+        double w[kWaves];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double s = 0.0;
-            for (int w = 0; w < kWaves; ++w)
-                s += red[c][w];
-            out[c] = s;
-        }
+        for (int q = 0; q < kWaves; ++q)
+            w[q] = ((p[q][0] + p[q][1]) + p[q][2]) + p[q][3];
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q)
+            s += w[q];
     }
     __syncthreads();
+    return s;
 }
 
 // Group g of a replica's tile partials -> group partial g.
 template <typename R>
-__device__ void group_reduce(const ReplicaDev<R>& r, int g, double (*red)[kWaves])
+__device__ void group_reduce(const ReplicaDev<R>& r, int g, BlockSums& red)
 {
     const int lo = g * kGroupTiles;
     const int cnt = min(kGroupTiles, r.blocks - lo);
@@ -455,22 +493,17 @@ __device__ void group_reduce(const ReplicaDev<R>& r, int g, double (*red)[kWaves
         for (int c = 0; c < 4; ++c)
             v[c] = p[c];
     }
-    double out[4];
-    block_sum4(v, out, red);
-    if (threadIdx.x == 0) {
-        double* q = r.group_partials + 4 * (int64_t)g;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            q[c] = out[c];
-    }
+    const double s = block_sum4(v, red);
+    if (threadIdx.x < 4)
+        r.group_partials[4 * (int64_t)g + threadIdx.x] = s;
 }
 
 // All group partials -> record `slot` (m = sum mu S / sum mu, E).
 template <typename R>
-__device__ void final_reduce(const ReplicaDev<R>& r, int slot, double (*red)[kWaves])
+__device__ void final_reduce(const ReplicaDev<R>& r, int slot, BlockSums& red)
 {
     const int n_groups = (r.blocks + kGroupTiles - 1) / kGroupTiles;
-    double tot[4] = {0.0, 0.0, 0.0, 0.0};
+    double tot = 0.0;
     for (int q0 = 0; q0 < n_groups; q0 += kBlockThreads) {
         double v[4] = {0.0, 0.0, 0.0, 0.0};
         const int q = q0 + (int)threadIdx.x;
@@ -480,19 +513,11 @@ __device__ void final_reduce(const ReplicaDev<R>& r, int slot, double (*red)[kWa
             for (int c = 0; c < 4; ++c)
                 v[c] = p[c];
         }
-        double out[4];
-        block_sum4(v, out, red);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 4; ++c)
-                tot[c] += out[c];
+        tot += block_sum4(v, red);
     }
-    if (threadIdx.x == 0) {
-        double* out = r.records + 4 * (r.rec_pos + slot);
+    if (threadIdx.x < 4) {
         const double f = r.mu_ref * r.inv_mu_total;
-        out[0] = tot[0] * f;
-        out[1] = tot[1] * f;
-        out[2] = tot[2] * f;
-        out[3] = -r.mu_ref * tot[3];
+        r.records[4 * (r.rec_pos + slot) + threadIdx.x] = threadIdx.x < 3 ? tot * f : -r.mu_ref * tot;
     }
 }
 
@@ -572,9 +597,11 @@ __device__ __forceinline__ void add_thermal(const MaterialDev<R>& m, const R g[3
 // Records: the state the predictor reads at step k >= 1 is the state after
 // step k - 1, and its exchange field is at hand, so the predictor leaves
 // per-tile partials of m and E for record k - 1; the corrector of the same
-// step sums them by groups, and the tile-0 workgroup of the next predictor
-// (or of the measuring pass at the end of the chunk) adds the groups into
-// the record.  The chunk's last record is completed by k_finish.
+// step sums them by groups, and the next predictor (or the measuring pass at
+// the end of the chunk) adds the groups into the record, each by work items
+// of its own beside the tiles (after a tile of their own these sums were a
+// sixth of a predictor launch on 4,096 spins).  The chunk's last record is
+// completed by k_finish.
 // ---------------------------------------------------------------------------
 // The sites of one tile (PS: per-site materials or axes; otherwise the
 // material is read once into scalar registers).
@@ -635,7 +662,7 @@ __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps
 {
     __shared__ Shared<R> sh;
     __shared__ TileLds<R> tl;
-    __shared__ double red[4][kWaves];
+    __shared__ BlockSums red;
     const int W = *n_work;
     int staged = -1;
     for (TileIter it(W, remap); it.more(); it.next()) {
@@ -645,6 +672,17 @@ __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps
         if (MEASURE ? (!(r.flags & kRecord) || (k == 0 && nsteps <= 0)) : (k >= nsteps))
             continue;   // uniform over the block
         const bool recording = (r.flags & kRecord) != 0;
+        if (w.block < 0) {
+            // the replica's first reduction item: group partials left by the
+            // previous corrector -> their record
+            if (recording && w.block == -1) {
+                if (!MEASURE && k >= 2)
+                    final_reduce(r, k - 2, red);
+                else if (MEASURE && k == 0 && nsteps >= 2)
+                    final_reduce(r, nsteps - 2, red);
+            }
+            continue;
+        }
         const bool partials = recording && (MEASURE || k >= 1);
         const int par = (r.parity + (MEASURE ? (k == 0 ? nsteps : 0) : k)) & 1;
         const R* __restrict__ S = r.S[par];
@@ -666,22 +704,9 @@ __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps
         else
             predict_sites<R, MEASURE, 0>(r, S, sh, tl, i0, wb, k, partials, v);
         if (partials) {
-            double out[4];
-            block_sum4(v, out, red);
-            if (threadIdx.x == 0) {
-                double* p = r.partials + 4 * (int64_t)w.block;
-                p[0] = out[0];
-                p[1] = out[1];
-                p[2] = out[2];
-                p[3] = out[3];
-            }
-        }
-        // group partials left by the previous corrector -> their record
-        if (recording && w.block == 0) {
-            if (!MEASURE && k >= 2)
-                final_reduce(r, k - 2, red);
-            else if (MEASURE && k == 0 && nsteps >= 2)
-                final_reduce(r, nsteps - 2, red);
+            const double sum = block_sum4(v, red);
+            if (threadIdx.x < 4)
+                r.partials[4 * (int64_t)w.block + threadIdx.x] = sum;
         }
     }
 }
@@ -694,8 +719,7 @@ __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps
 // S' = (S + dS dt)/|S + dS dt| has S.S' = 1/|S + dS dt|, and
 // S + dS dt / 2 = (S + S'/(S.S'))/2 comes from S and S' (whatever the
 // rounding of the predictor's normalisation, which cancels in S'/(S.S')).
-// Workgroups whose tile opens a group of kGroupTiles also sum that group of
-// the predictor's partials.
+// Reduction items sum the groups of kGroupTiles of the predictor's partials.
 // ---------------------------------------------------------------------------
 
 template <typename R, int V>
@@ -747,7 +771,7 @@ __global__ SLLG_STEP_ATTRS void k_correct(const ReplicaDev<R>* __restrict__ reps
 {
     __shared__ Shared<R> sh;
     __shared__ TileLds<R> tl;
-    __shared__ double red[4][kWaves];
+    __shared__ BlockSums red;
     const int W = *n_work;
     int staged = -1;
     for (TileIter it(W, remap); it.more(); it.next()) {
@@ -755,6 +779,11 @@ __global__ SLLG_STEP_ATTRS void k_correct(const ReplicaDev<R>* __restrict__ reps
         const ReplicaDev<R>& r = reps[w.replica];
         if (k >= r.nsteps)
             continue;
+        if (w.block < 0) {   // reduction item g = -1 - block: that group of the predictor's partials
+            if ((r.flags & kRecord) && k >= 1)
+                group_reduce(r, -1 - w.block, red);
+            continue;
+        }
         const R* __restrict__ Sp = r.Sp;
         const int T = r.tile;
         const int i0 = w.block * T, wb = i0 - r.halo;
@@ -774,8 +803,6 @@ __global__ SLLG_STEP_ATTRS void k_correct(const ReplicaDev<R>* __restrict__ reps
             correct_sites<R, V>(r, Sc, Sp, Sn, sh, tl, i0, wb, k);
         else
             correct_sites<R, 0>(r, Sc, Sp, Sn, sh, tl, i0, wb, k);
-        if ((r.flags & kRecord) && k >= 1 && (w.block % kGroupTiles) == 0)
-            group_reduce(r, w.block / kGroupTiles, red);
     }
 }
 
@@ -786,7 +813,7 @@ template <typename R>
 __global__ __launch_bounds__(kBlockThreads) void k_finish(const ReplicaDev<R>* __restrict__ reps, int mode,
                                                           int slot)
 {
-    __shared__ double red[4][kWaves];
+    __shared__ BlockSums red;
     const ReplicaDev<R>& r = reps[blockIdx.x];
     if (!(r.flags & kRecord) || (mode == 0 && (r.nsteps <= 0 || (r.flags & kBrick))))
         return;   // a brick chunk's records come from its own items
@@ -1253,17 +1280,18 @@ __global__ void k_scatter_records(const double* __restrict__ rec, int count,
     }
 }
 
-// Running block sums for thermal averages, one thread per replica:
+// Running block sums for thermal averages, one workgroup per replica:
 // acc[b] += (|m|, m_x, m_y, m_z, E) for every record of this chunk whose
 // step falls in averaging block b = (step - avg_first) / avg_block_len.
 // Each replica's samples are added one by one in step order, so the sums do
 // not depend on the chunking or on the other replicas of the batch.
 template <typename R>
-__global__ void k_accumulate(const ReplicaDev<R>* __restrict__ reps, int n_rep)
+__global__ __launch_bounds__(64) void k_accumulate(const ReplicaDev<R>* __restrict__ reps)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n_rep && !(reps[j].flags & kBrick))
-        accumulate_records(reps[j]);
+    __shared__ double buf[64][5];
+    const ReplicaDev<R>& r = reps[blockIdx.x];
+    if (!(r.flags & kBrick))
+        accumulate_records(r, buf);
 }
 
 }  // namespace
@@ -1446,7 +1474,7 @@ hipError_t launch_accumulate(const ReplicaDev<R>* reps, int n_rep, hipStream_t s
 {
     if (n_rep <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL((k_accumulate<R>), dim3((n_rep + 63) / 64), dim3(64), 0, st, reps, n_rep);
+    hipLaunchKernelGGL((k_accumulate<R>), dim3(n_rep), dim3(64), 0, st, reps);
     return hipGetLastError();
 }
 

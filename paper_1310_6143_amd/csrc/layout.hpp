@@ -162,7 +162,8 @@ constexpr int kBrickMinEdge = 5;
 // (the long-range step alone, longrange.hip).
 enum FusedKind : int32_t { kKindGeneric = 0, kKindSc6 = 1, kKindBcc8 = 2, kKindBcc14 = 3, kKindLong = 4 };
 constexpr int kLongReach = 4;
-constexpr int kLongHead = 8;   // words before the column list: first column of each of the four waves, their end
+constexpr int kLongColumns = (2 * kLongReach + 1) * (2 * kLongReach + 1);   // (dx, dy) columns of links at most
+constexpr int kLongHead = 32;   // 8 words for each of the four waves: its first column, its columns of reach 4 .. 0
 
 __host__ __device__ constexpr int kind_basis(int kind)
 {
@@ -271,6 +272,7 @@ struct ReplicaDev {
     int32_t nsteps;                 // steps this replica takes in the current chunk
     int32_t flags;                  // ReplicaFlags
     int32_t n_patterns;             // stencil patterns (kStencil)
+    int32_t n_entries;              // their entries together (kStencil)
     int32_t tile;                   // sites per tile: tile_for(n, sizeof(R))
     int32_t w_len;                  // entries per pattern in the wide form (kWide)
     const uint16_t* w_pid;          // [n] pattern of each site (kWide)
@@ -296,15 +298,17 @@ struct ReplicaDev {
     // words of near links, then as many of far ones, to whole 16 bytes
     const uint32_t* b_links;
     int32_t b_near, b_far;          // pairs in use, the most over the classes
-    // long-range step: [kLongHead] column ranges of the four waves, then
-    // (slot offset, reach) of each column; [columns][2 kLongReach + 1] J / mu_ref
+    // long-range step: [kLongHead] the waves' columns, then each column's slot
+    // offset; [columns][2 kLongReach + 1] J / mu_ref from the column's -reach on
     const int32_t* l_head;
     const R* l_J;
+    int32_t l_columns;
+    int32_t l_pad;
 };
 
 struct WorkItem {
     int32_t replica;
-    int32_t block;                  // tile index within the replica
+    int32_t block;                  // tile index within the replica; -1 - g: the sums of its group g of tiles
 };
 
 }  // namespace sllg

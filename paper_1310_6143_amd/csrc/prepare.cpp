@@ -1038,6 +1038,7 @@ void fill_parameters(ReplicaDev<R>& rec, const HostStructure& s, const HostMater
         nent += (int32_t)p.size();
     rec.f_nent = nent;
     rec.n_patterns = s.stencil ? (int32_t)s.pat_start.size() - 1 : s.wide ? (int32_t)s.w_near.size() : 0;
+    rec.n_entries = s.stencil ? (int32_t)s.pat_start.back() : 0;
     rec.w_len = s.wide ? s.w_len : 0;
     rec.dm_cells = s.demag.on ? (int32_t)s.demag.cells : 0;
     rec.dm_chunks = s.demag.on ? demag_chunks(s.demag.cells) : 0;
