@@ -106,19 +106,24 @@ __device__ __forceinline__ V3<double> bload3(__amdgpu_buffer_rsrc_t rs, int off,
 
 // Neighbour tables a workgroup stages in LDS: the J table and, for the
 // stencil layout, every pattern entry as (byte offset of the neighbour's spin
-// from the site's own, J of the link).
+// from the site's own, J of the link), with exchange tensors (byte offset,
+// type of the link) in the same slot.
 template <typename R>
 struct PatEntry;
 template <>
 struct PatEntry<float> {
     int32_t off;
     float J;
+    __device__ void set_type(int t) { J = __int_as_float(t); }
+    __device__ int type() const { return __float_as_int(J); }
 };
 template <>
 struct PatEntry<double> {
     int32_t off;
-    int32_t pad;
+    int32_t link_type;
     double J;
+    __device__ void set_type(int t) { link_type = t; }
+    __device__ int type() const { return link_type; }
 };
 
 template <typename R>
@@ -128,9 +133,8 @@ struct Shared {
     uint16_t pat_far[kMaxPatterns];
     PatEntry<R> pat[kMaxPatternEntries];
     // exchange tensors (kTensor): jm[type], jm[kMaxTypes] = 0 for padding
-    // entries, and the type of every pattern entry
-    R jm[kMaxTypes + 1][9];
-    uint8_t ptype[kMaxPatternEntries];
+    // entries; rows of 12 so that a matrix is read 16 bytes at a time
+    alignas(16) R jm[kMaxTypes + 1][12];
 };
 
 // The tile being integrated: spins of sites [i0 - halo, i0 + tile + halo)
@@ -174,9 +178,10 @@ __device__ __forceinline__ void stage_tables(const ReplicaDev<R>& r, Shared<R>& 
             const R J = __shfl(jv, raw[j] & 15, 64);   // every lane takes part
             if (q < ne) {
                 sh.pat[q].off = (raw[j] >> 4) * (int)(3 * sizeof(R));
-                sh.pat[q].J = (raw[j] >> 4) != 0 ? J : (R)0;   // offset 0: padding
-                if (tensor)
-                    sh.ptype[q] = (raw[j] >> 4) != 0 ? (uint8_t)(raw[j] & 15) : (uint8_t)kMaxTypes;
+                if (tensor)   // offset 0: padding
+                    sh.pat[q].set_type((raw[j] >> 4) != 0 ? (raw[j] & 15) : kMaxTypes);
+                else
+                    sh.pat[q].J = (raw[j] >> 4) != 0 ? J : (R)0;
             }
         }
         if (t <= np)
@@ -249,6 +254,26 @@ __device__ __forceinline__ int site_bytes(int x)
 // Links per batch of the long-row SELL gathers.
 constexpr int kSellBatch = 8;
 
+// A 3x3 row-major coupling matrix of the LDS table, 16 bytes a read.  LDS
+// instructions bound a step with tensors: rows of 9 took five to nine reads a
+// link and the link's type another before them.  1,769,472 bcc spins with 14
+// tensors, FP32: predictor 56.4 -> 47.7 us, corrector 47.8 -> 40.1 (two sites
+// of one pattern per thread sharing each read: 54 and 49, too few waves).
+template <typename R>
+__device__ __forceinline__ void load_matrix(const R* row, R M[9])
+{
+    constexpr int W = 16 / (int)sizeof(R);
+    typedef R vec __attribute__((ext_vector_type(W)));
+#pragma unroll
+    for (int q = 0; q < 8; q += W) {
+        const vec v = *(const vec*)(row + q);
+#pragma unroll
+        for (int u = 0; u < W; ++u)
+            M[q + u] = v[u];
+    }
+    M[8] = row[8];
+}
+
 // h += M S_j for a 3x3 row-major coupling matrix M.
 template <typename R>
 __device__ __forceinline__ void add_link(V3<R>& h, const R* M, const V3<R>& sj)
@@ -265,7 +290,9 @@ __device__ __forceinline__ void add_coupled(V3<R>& h, bool tensor, const Shared<
                                             const V3<R>& sj)
 {
     if (TX && tensor) {
-        add_link(h, sh.jm[type], sj);
+        R M[9];
+        load_matrix(sh.jm[type], M);
+        add_link(h, M, sj);
     } else {
         h.x += J * sj.x;
         h.y += J * sj.y;
@@ -350,26 +377,26 @@ __device__ __forceinline__ V3<R> exchange_sum(const ReplicaDev<R>& r, const R* _
             for (int k = b; k < f; ++k) {
                 const PatEntry<R> pe = sh.pat[k];
                 const V3<R> sj = bload3(rs, ib + pe.off, R(0));
-                add_coupled<R, TX>(hn, tensor, sh, TX ? sh.ptype[k] : 0, pe.J, sj);
+                add_coupled<R, TX>(hn, tensor, sh, TX ? pe.type() : 0, pe.J, sj);
             }
         } else {
             SLLG_UNROLL(SLLG_NEAR_UNROLL)
             for (int k = b; k < f; ++k) {
                 const PatEntry<R> pe = sh.pat[k];
                 const V3<R> sj = wload3(tl.win, wbyte + pe.off);
-                add_coupled<R, TX>(hn, tensor, sh, TX ? sh.ptype[k] : 0, pe.J, sj);
+                add_coupled<R, TX>(hn, tensor, sh, TX ? pe.type() : 0, pe.J, sj);
             }
         }
         if (far) {
 #pragma unroll
             for (int q = 0; q < kFarRegs; ++q)
-                add_coupled<R, TX>(hf, tensor, sh, TX ? sh.ptype[f + q] : 0, fp[q].J, fr[q]);
+                add_coupled<R, TX>(hf, tensor, sh, TX ? fp[q].type() : 0, fp[q].J, fr[q]);
         }
         SLLG_UNROLL(SLLG_GATHER_UNROLL)
         for (int k = f + kFarRegs; k < e; ++k) {
             const PatEntry<R> pe = sh.pat[k];
             const V3<R> sj = bload3(rs, ib + pe.off, R(0));
-            add_coupled<R, TX>(hf, tensor, sh, TX ? sh.ptype[k] : 0, pe.J, sj);
+            add_coupled<R, TX>(hf, tensor, sh, TX ? pe.type() : 0, pe.J, sj);
         }
     } else {
         overlap();
@@ -1149,7 +1176,7 @@ __device__ __forceinline__ V3<R> exchange_sum_global(const ReplicaDev<R>& r, con
                 const int kk = k + u < e ? k + u : e - 1;
                 const PatEntry<R> pe = sh.pat[kk];
                 J[u] = k + u < e ? pe.J : (R)0;
-                ty[u] = tensor ? (k + u < e ? (int)sh.ptype[kk] : kMaxTypes) : 0;
+                ty[u] = tensor ? (k + u < e ? pe.type() : kMaxTypes) : 0;
                 sj[u] = load3((const R*)(si + pe.off), 0);
             }
 #pragma unroll
