@@ -470,13 +470,16 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  *                     2^20 spins; smaller systems take the brick step where
  *                     their lattice has the simple-cubic or bcc links and at
  *                     least 5 cells on each periodic axis (with second
- *                     neighbours up to 150,000 spins in FP32, 100,000 in
- *                     FP64) and the sites of a class (basis site, first,
- *                     inner or last cell of each axis) list their links in
- *                     one order, with the spins of the two-launch step bit
- *                     for bit, else the two-launch step; 2: the fused step
- *                     whenever the system qualifies; 0: always the
- *                     two-launch step
+ *                     neighbours up to 100,000 spins) and the sites of a
+ *                     class (basis site, first, inner or last cell of each
+ *                     axis) list their links in one order, with the spins
+ *                     of the two-launch step bit for bit, else the
+ *                     two-launch step.  Rows too many for the LDS tables
+ *                     that are one set of links up to 4 cells away on a
+ *                     periodic simple-cubic grid, with one material and
+ *                     scalar exchange, take the long-range step at any
+ *                     size.  2: the fused step whenever the system
+ *                     qualifies; 0: always the two-launch step
  *   "fused_tile_x", "fused_tile_y", "fused_planes", "fused_threads"
  *                     shape of the fused step's work items: a tile of
  *                     tile_x x tile_y cell columns marched through `planes`
@@ -497,7 +500,7 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  * queued work);
  * "lattice": 0 none declared, 1 declared, 2 declared and the fused step can
  * take its structure; "fused_active": 1 when the next integration runs the
- * fused step; "brick_active": 1 when it runs the brick step; the fused_* shape keys read the shape in use;
+ * fused step; "brick_active": 1 when it runs the brick or the long-range step; the fused_* shape keys read the shape in use;
  * "halo": neighbours with |column - row| up to this many
  * sites are read from the tile's window in LDS, the rest from HBM (-1 unset).
  */

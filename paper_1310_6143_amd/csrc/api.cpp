@@ -279,9 +279,11 @@ void ensure_device(sllg_system* s)
 }
 
 // Spins from which the fused step is the default (below it shallow launches
-// win: measured per step, FP32, bcc with second neighbours, 0.52M spins 23.7
-// against 25.3 us of the two-launch step, 1.02M 37.9 against 39.2; nearest
-// neighbours alone, 1.02M spins 32.4 against 32.0 us of the brick step).
+// win without autotuning: measured per step, FP32, bcc with second
+// neighbours, 0.52M spins 23.7 us both, 1.02M 37.9 against 34.9 of the
+// two-launch step; nearest neighbours alone, 1.02M spins 32.4 against 32.0
+// us of the brick step.  Its tuned shapes, 30.6 and 25.7 us there, are only
+// known to a caller who tunes, for whom "fused" = 2 is the switch).
 constexpr int64_t kFusedMinSpins = int64_t(1) << 20;
 
 bool fused_wanted(const sllg_system* s)
@@ -294,18 +296,20 @@ bool fused_wanted(const sllg_system* s)
 // fused step's size, and with second neighbours only while a launch is bound
 // by its latencies.  There the bricks' neighbours (2.4 predictors per site
 // against 1.8 to 2) make the arithmetic count early: measured per step
-// against the two-launch step, FP32 8.8 and 14.3 us at 65,536 spins, 13.4
-// and 15.0 at 128,000, 24.0 and 17.2 at 221,184; FP64 12.4 and 17.2 at
-// 65,536, 20.1 and 17.5 at 128,000.  With nearest neighbours it wins over
-// the whole range (FP32 5.3 against 13.0 us at 65,536 bcc spins, 32.0 against
-// 35.6 at 1,024,000; FP64 7.3 and 16.0, 55.3 and 69.3).
+// against the two-launch step, FP32 8.8 and 11.6 us at 65,536 spins, 13.4
+// and 12.1 at 128,000; FP64 12.4 and 15.1 at 65,536, 20.1 and 16.2 at
+// 128,000.  With nearest neighbours it wins over the whole range (FP32 5.3
+// against 10.7 us at 65,536 bcc spins, 32.0 against 32.2 at 1,024,000; FP64
+// 7.3 and 14.2, 55.7 and 64.8).
+constexpr int64_t kBrickMaxSecond = 100000;
+
 bool brick_wanted(const sllg_system* s)
 {
     if (s->opt_fused != 1 || (fused_wanted(s) && !s->st.far.on))
         return false;
     if (s->st.far.on)
         return true;   // the long-range step, at any size
-    return s->st.lat.kind != kKindBcc14 || s->n <= (s->prec == SLLG_FP32 ? 150000 : 100000);
+    return s->st.lat.kind != kKindBcc14 || s->n <= kBrickMaxSecond;
 }
 
 Engine& engine(sllg_system* s)

@@ -12,8 +12,8 @@
 // instructions and two loads a link).  Here a workgroup copies the spins of
 // an 8 x 8 x 4 cell tile and four cells around it into LDS once.  A lane
 // holds a run of four sites along z: for each column (dx, dy) of links it
-// reads the column's spins once and uses each for up to four sites, so a link costs three FMAs and a third of
-// an LDS read.  The columns are ordered by their reach along z, so each loop
+// reads the column's spins once and uses each for up to four sites, so a link
+// costs three FMAs and a third of an LDS read.  The columns are ordered by their reach along z, so each loop
 // over them has its run unrolled, and their couplings and offsets come from
 // LDS (scalar loads, which drain with the LDS reads, took 29.4 us a step for
 // 110,592 FP32 spins against 26.9 here; the wide form 70.6, and FP64 115.4

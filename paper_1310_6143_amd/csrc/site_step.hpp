@@ -1,7 +1,7 @@
-// Pieces the single-launch steps (fused.hip, brick.hip) share: the record of
-// a replica from its work items' sums, and, for the plane march, the record
-// terms, predictor and corrector of one site of a uniform material with
-// scalar exchange.
+// Pieces that the steps on declared or found lattices (fused.hip, brick.hip,
+// longrange.hip) share: the record of a replica from its work items' sums,
+// and, for the plane march, the record terms, predictor and corrector of one
+// site of a uniform material with scalar exchange.
 #pragma once
 
 #include "device_common.hpp"
