@@ -36,7 +36,7 @@ COUNTER_FILES = {
     "two_launch": (os.path.join(ROOT, "profiles", "bcc160_step_hbm_counters.md"),
                    ["kernels.hip", "device_common.hpp"]),
     "fused": (os.path.join(ROOT, "profiles", "bcc160_fused_step_counters.md"),
-              ["fused.hip", "device_common.hpp"]),
+              ["fused.hip", "site_step.hpp", "device_common.hpp"]),
 }
 
 
