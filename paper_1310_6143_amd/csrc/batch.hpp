@@ -23,6 +23,7 @@
 #include <thread>
 #include <vector>
 
+#include "item_list.hpp"
 #include "kernels.hpp"
 #include "layout.hpp"
 #include "prepare.hpp"
@@ -454,7 +455,7 @@ public:
         (void)hipFree(d_work_);
         (void)hipFree(d_fwork_);
         for (BrickList& b : brick_) {
-            (void)hipFree(b.d);
+            (void)hipFree(b.items.d);
             (void)hipFree(b.table);
         }
         (void)hipFree(d_nwork_);
@@ -1172,18 +1173,25 @@ public:
                 const std::vector<uint32_t> tab = brick_table(kind);
                 if (tab.empty())
                     fail(SLLG_E_STATE, "brick table does not fit its workgroup");
-                hip_check(hipMalloc(&b.table, tab.size() * sizeof(uint32_t)), "hipMalloc(brick table)");
-                hip_check(hipMemcpy(b.table, tab.data(), tab.size() * sizeof(uint32_t), hipMemcpyHostToDevice),
-                          "upload brick table");
+                uint32_t* d = nullptr;
+                hip_check(hipMalloc(&d, tab.size() * sizeof(uint32_t)), "hipMalloc(brick table)");
+                const hipError_t e = hipMemcpy(d, tab.data(), tab.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+                if (e != hipSuccess)
+                    (void)hipFree(d);   // b.table stays unset: the next call uploads it again
+                hip_check(e, "upload brick table");
                 b.resident = std::max(brick_resident_blocks<R>(device_, kind) & ~7, 8);
+                b.table = d;
             }
-            if (n > b.cap) {
+            if (n > b.items.cap)
                 drop_graph();
-                (void)hipFree(b.d);
-                b.d = nullptr;
-                b.cap = std::max<int64_t>(n, 2 * b.cap);
-                hip_check(hipMalloc(&b.d, sizeof(FusedItem) * (size_t)b.cap + sizeof(int)), "hipMalloc(bricks)");
-            }
+            b.items.reserve(
+                n,
+                [](size_t bytes) {
+                    void* p = nullptr;
+                    hip_check(hipMalloc(&p, bytes), "hipMalloc(bricks)");
+                    return p;
+                },
+                [](void* p) { (void)hipFree(p); });
             // as for the tiles: at most the resident workgroups, and always
             // those for a changing batch (one graph serves it)
             int grid = std::min((n + 7) & ~7, b.resident);
@@ -1192,11 +1200,11 @@ public:
             if (grid != b.grid)
                 drop_graph();
             b.grid = grid;
-            if (b.d) {
+            if (b.items.d) {
                 if (n > 0)
-                    hip_check(hipMemcpy(b.d, all.data(), sizeof(FusedItem) * (size_t)n, hipMemcpyHostToDevice),
+                    hip_check(hipMemcpy(b.items.d, all.data(), sizeof(FusedItem) * (size_t)n, hipMemcpyHostToDevice),
                               "upload bricks");
-                hip_check(hipMemcpy(b.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
+                hip_check(hipMemcpy(b.items.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
             }
             bricks_ += n;
         }
@@ -1505,9 +1513,9 @@ private:
         for (int kind = 1; kind < kBrickKinds && e == hipSuccess; ++kind) {
             const BrickList& b = brick_[kind];
             if (b.grid > 0 && kind == kKindLong)
-                e = launch_long<R>(d_reps_, b.d, b.count(), b.grid, k, remap_, measure, st);
+                e = launch_long<R>(d_reps_, b.items.d, b.items.count(), b.grid, k, remap_, measure, st);
             else if (b.grid > 0)
-                e = launch_brick<R>(d_reps_, b.d, b.count(), b.table, b.grid, k, remap_, measure, kind, st);
+                e = launch_brick<R>(d_reps_, b.items.d, b.items.count(), b.table, b.grid, k, remap_, measure, kind, st);
         }
         return e;
     }
@@ -1643,12 +1651,10 @@ private:
     // brick step: items and their count per kind, and the kind's site tables
     static constexpr int kBrickKinds = kKindLong + 1;
     struct BrickList {
-        FusedItem* d = nullptr;   // [cap] items, then their count
-        int64_t cap = 0;
+        ItemList<FusedItem> items;
         int grid = 0;
         int resident = 8;
         uint32_t* table = nullptr;
-        int* count() const { return reinterpret_cast<int*>(reinterpret_cast<char*>(d) + sizeof(FusedItem) * (size_t)cap); }
     };
     BrickList brick_[kBrickKinds];
     bool brick_on_ = false;
