@@ -12,14 +12,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstdlib>
 #include <cstdint>
 #include <cstring>
 #include <map>
 #include <memory>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -27,6 +25,7 @@
 #include "kernels.hpp"
 #include "layout.hpp"
 #include "prepare.hpp"
+#include "widen.hpp"
 
 #ifndef SLLG_DEFAULT_REMAP
 #define SLLG_DEFAULT_REMAP 1
@@ -1541,55 +1540,14 @@ private:
     // False when no host threads can be had.
     bool widen_staged(const R* src, size_t total, double* out, hipStream_t st)
     {
-        const size_t pieces = (total + kPiece - 1) / kPiece;
-        const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-        const size_t T = std::min<size_t>(8, hw);
-        std::atomic<size_t> ready{0};          // pieces that have arrived (or pieces + 1: stop)
-        std::vector<std::atomic<size_t>> done(pieces);   // threads that have widened each piece
-        for (auto& d : done)
-            d.store(0);
-        auto widen = [&](size_t w) {
-            for (size_t k = 0; k < pieces; ++k) {
-                for (size_t seen; (seen = ready.load(std::memory_order_acquire)) <= k;)
-                    std::this_thread::yield();
-                if (ready.load(std::memory_order_acquire) > pieces)
-                    return;
-                const size_t len = std::min(kPiece, total - k * kPiece);
-                const size_t lo = len * w / T, hi = len * (w + 1) / T;
-                const R* from = pinned_spins_ + (k & 1) * kPiece;
-                double* to = out + k * kPiece;
-                for (size_t i = lo; i < hi; ++i)
-                    to[i] = (double)from[i];
-                done[k].fetch_add(1, std::memory_order_release);
-            }
-        };
-        std::vector<std::thread> pool;
-        pool.reserve(T);
-        hipError_t e = hipSuccess;
-        bool threads = true;
-        try {
-            for (size_t w = 0; w < T; ++w)
-                pool.emplace_back(widen, w);
-        } catch (const std::system_error&) {
-            threads = false;
-        }
-        for (size_t k = 0; k < pieces && threads && e == hipSuccess; ++k) {
-            while (k >= 2 && done[k - 2].load(std::memory_order_acquire) < T)
-                std::this_thread::yield();
-            const size_t len = std::min(kPiece, total - k * kPiece);
-            e = hipMemcpyAsync(pinned_spins_ + (k & 1) * kPiece, src + k * kPiece, len * sizeof(R),
-                               hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess)
-                e = hipStreamSynchronize(st);
-            if (e == hipSuccess)
-                ready.store(k + 1, std::memory_order_release);
-        }
-        if (e != hipSuccess || !threads)
-            ready.store(pieces + 1, std::memory_order_release);
-        for (auto& th : pool)
-            th.join();
-        hip_check(e, "download spins");
-        return threads;
+        const size_t threads = std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency()));
+        return widen_pieces(
+            pinned_spins_, kPiece, total, out, threads,
+            [&](size_t first, size_t len, R* to) {
+                hip_check(hipMemcpyAsync(to, src + first, len * sizeof(R), hipMemcpyDeviceToHost, st), "download spins");
+                hip_check(hipStreamSynchronize(st), "download spins");
+            },
+            [](auto& f, size_t w) { return std::thread([&f, w] { f(w); }); });
     }
 
     void drop_graph()

@@ -1,5 +1,6 @@
 """Host parts of the library that need no GPU, compiled on their own: the
-device work lists around a failed allocation."""
+device work lists around a failed allocation, and the staged read-back around
+threads or copies that fail."""
 import os
 import subprocess
 
@@ -8,7 +9,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.parametrize("name", ["item_list_test"])
+@pytest.mark.parametrize("name", ["item_list_test", "widen_test"])
 def test_host_part(name, tmp_path):
     exe = tmp_path / name
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-pthread",
