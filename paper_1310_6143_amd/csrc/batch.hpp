@@ -956,7 +956,7 @@ public:
         const R* src = r.S[r.parity];
         quiesce();
         hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-        if (total >= kStagedReals && staging() && widen_staged(src, total, out, st))
+        if (staged_read(total) && widen_staged(src, total, out, st))
             return;
         if constexpr (sizeof(R) == 8) {
             hip_check(hipMemcpy(out, src, total * sizeof(R), hipMemcpyDeviceToHost), "download spins");
@@ -1520,9 +1520,9 @@ private:
     }
     bool takes_brick(const Slot& sl) const { return sl.used && brick_on_ && !fused_mode_ && sl.b_kind != 0; }
 
-    // Reals from which get_spins takes the staged path, and reals per piece.
-    // (Measured in FP32: 0.39M reals 0.2 ms either way.)
-    static constexpr size_t kStagedReals = size_t(1) << 20;
+    // Reals from which get_spins takes the staged path, the first time and
+    // again (staged_read), and reals per piece.
+    static constexpr size_t kStagedFirst = size_t(1) << 21, kStagedReals = size_t(1) << 20;
     static constexpr size_t kPiece = (size_t(4) << 20) / sizeof(R);
 
     // Two pinned pieces, kept for the batch's lifetime; false when they
@@ -1535,6 +1535,20 @@ private:
             pinned_spins_ = nullptr;
         }
         return pinned_spins_ != nullptr;
+    }
+
+    // Whether a read of `total` reals goes through the pieces.  Allocating
+    // them takes 0.9 ms, as much as they save one read of 2^21 reals (FP64,
+    // first read on a new system: 1.0M reals 0.95 ms plain and 1.4 staged,
+    // 2.1M 2.0 and 2.0; again 0.8 and 0.33, 1.6 and 0.50), so below that the
+    // first read of a batch is the plain one.
+    bool staged_read(size_t total)
+    {
+        if (total < kStagedReals)
+            return false;
+        const bool first = !read_large_;
+        read_large_ = true;
+        return (!first || total >= kStagedFirst) && staging();
     }
 
     // False when no host threads can be had.
@@ -1565,6 +1579,7 @@ private:
     std::vector<ReplicaDev<R>> host_reps_;
     ReplicaDev<R>* pinned_reps_ = nullptr;   // pinned staging of host_reps_
     R* pinned_spins_ = nullptr;              // two pieces of get_spins, once used
+    bool read_large_ = false;                // get_spins has read kStagedReals or more
     std::vector<char> active_;               // replicas in the current work lists (used, nsteps > 0)
     bool lists_dirty_ = true;
     int64_t graph_captures_ = 0;
