@@ -469,8 +469,10 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  *                     system qualifies (sllg_set_lattice) and has at least
  *                     2^20 spins; smaller systems take the brick step where
  *                     their lattice has the simple-cubic or bcc links and at
- *                     least 5 cells on each periodic axis (with second
- *                     neighbours up to 100,000 spins) and the sites of a
+ *                     least 5 cells on each periodic axis, the lattice
+ *                     fills the step's bricks well enough for them to be
+ *                     the faster way (with second neighbours: at most 256
+ *                     bricks of 8 x 4 x 4 cells) and the sites of a
  *                     class (basis site, first, inner or last cell of each
  *                     axis) list their links in one order, with the spins
  *                     of the two-launch step bit for bit, else the

@@ -291,25 +291,16 @@ bool fused_wanted(const sllg_system* s)
     return s->opt_fused == 2 || (s->opt_fused == 1 && s->n >= kFusedMinSpins);
 }
 
-// Whether the brick step is the default for a lattice of n spins (option
-// "fused" = 1; 0 takes the two-launch step, 2 the plane march): below the
-// fused step's size, and with second neighbours only while a launch is bound
-// by its latencies.  There the bricks' neighbours (2.4 predictors per site
-// against 1.8 to 2) make the arithmetic count early: measured per step
-// against the two-launch step, FP32 8.8 and 11.6 us at 65,536 spins, 13.4
-// and 12.1 at 128,000; FP64 12.4 and 15.1 at 65,536, 20.1 and 16.2 at
-// 128,000.  With nearest neighbours it wins over the whole range (FP32 5.3
-// against 10.7 us at 65,536 bcc spins, 32.0 against 32.2 at 1,024,000; FP64
-// 7.3 and 14.2, 55.7 and 64.8).
-constexpr int64_t kBrickMaxSecond = 100000;
-
+// Whether the brick step is the default for a lattice (option "fused" = 1; 0
+// takes the two-launch step, 2 the plane march): below the fused step's size,
+// and where its bricks are the faster way (brick_pays).
 bool brick_wanted(const sllg_system* s)
 {
     if (s->opt_fused != 1 || (fused_wanted(s) && !s->st.far.on))
         return false;
     if (s->st.far.on)
         return true;   // the long-range step, at any size
-    return s->st.lat.kind != kKindBcc14 || s->n <= kBrickMaxSecond;
+    return brick_pays(s->st.lat, s->n, s->prec == SLLG_FP32 ? 4 : 8);
 }
 
 Engine& engine(sllg_system* s)

@@ -294,6 +294,21 @@ static void for_each_link(const HostStructure& s, int64_t i, F&& fn)
     }
 }
 
+bool brick_pays(const HostLattice& L, int64_t n, size_t real_bytes)
+{
+    if (L.kind != kKindSc6 && L.kind != kKindBcc8 && L.kind != kKindBcc14)
+        return false;
+    int c[3];
+    brick_cells(L.kind, c);
+    const int64_t bricks =
+        (int64_t)((L.nx + c[0] - 1) / c[0]) * ((L.ny + c[1] - 1) / c[1]) * ((L.nz + c[2] - 1) / c[2]);
+    if (L.kind == kKindBcc14)
+        return bricks <= 256;   // compute units of the MI355X
+    const double layers = L.per[2] ? 1.0 : std::min(1.0, (double)L.nz / c[2]);
+    const double spins = 256.0 * (double)bricks * (0.5 + 0.5 * layers);   // of as many full bricks
+    return real_bytes == 4 ? spins <= 250e3 + 0.75 * (double)n : spins <= 120e3 + 0.93 * (double)n;
+}
+
 // Link words of the brick step's site classes (see HostStructure): the row
 // of a class is that of its sites (their stencil pattern, or the SELL rows
 // one by one), near links first, each link as the cell offset its class gives

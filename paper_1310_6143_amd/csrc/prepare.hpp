@@ -170,6 +170,26 @@ void detect_long(HostStructure& s);
 // on the fused step is the default.
 constexpr int64_t kBrickMaxSites = int64_t(1) << 20;
 
+// Whether the brick step is faster than the two-launch step on a lattice of n
+// spins of one of its kinds, below the fused step's size.  What counts is the
+// bricks, not the spins: on thin films, rods and lattices that cut them they
+// are partly empty, and a brick costs nearly as much.  Measured us per step,
+// brick and two-launch, 300 K with records:
+//  - second neighbours: two bricks fill a compute unit's LDS in FP32 and one
+//    does in FP64, so beyond one brick per unit a launch takes half as long
+//    again: FP32 9.0 and 11.9 with 256 bricks (65,536 spins), 13.6 and 12.3
+//    with 405 (93,312), 25.6 and 12.8 with 950 (5 x 5 x 1900 cells); FP64 12.7
+//    and 15.4, 20.2 and 16.1, 37.5 and 17.4.
+//  - nearest neighbours: the launch's share of a brick, and of the two-launch
+//    step's sites, are lines through the measurements.  FP32: simple cubic
+//    9.7 and 16.1 (64^3), 24.8 and 29.9 (96^3), 33.8 and 32.3 (101^3), 62.7
+//    and 32.8 (5 x 5 x 40000), 67 and 31.5 (1000 x 1000 x 1), 6.9 and 11.0
+//    (256 x 256 x 1); bcc 19.5 and 22.8 (64^3), 36.1 and 33.9 (80^3), 49 and
+//    21.6 (512 x 512 x 1).  FP64: 18.2 and 24.2, 52.4 and 52.8, 63 and 63.7,
+//    137 and 62.6, 137 and 60.5, 10.5 and 14.3; 32.2 and 37.8, 60.5 and 65.8,
+//    69.8 and 36.7.  A film of one layer costs about 5/8 of a full brick.
+bool brick_pays(const HostLattice& L, int64_t n, size_t real_bytes);
+
 // Whether the brick step can run on the structure in a precision (bytes per
 // real).  Its tables (set_lattice) exist for a compiled kind with at least kBrickMinEdge cells per periodic axis in which every
 // site of a class lists its links in the same order.
