@@ -480,7 +480,8 @@ sllg_status sllg_restore(sllg_system *sys, const void *buf, size_t bytes);
  *                     that are one set of links up to 4 cells away on a
  *                     periodic simple-cubic grid, with one material and
  *                     scalar exchange, take the long-range step at any
- *                     size.  2: the fused step whenever the system
+ *                     size where they have links enough (from some
+ *                     20 to 70 on) and fill its tiles of 8 x 8 x 4 cells.  2: the fused step whenever the system
  *                     qualifies; 0: always the two-launch step
  *   "fused_tile_x", "fused_tile_y", "fused_planes", "fused_threads"
  *                     shape of the fused step's work items: a tile of

@@ -298,9 +298,8 @@ bool brick_wanted(const sllg_system* s)
 {
     if (s->opt_fused != 1 || (fused_wanted(s) && !s->st.far.on))
         return false;
-    if (s->st.far.on)
-        return true;   // the long-range step, at any size
-    return brick_pays(s->st.lat, s->n, s->prec == SLLG_FP32 ? 4 : 8);
+    const size_t real_bytes = s->prec == SLLG_FP32 ? 4 : 8;
+    return s->st.far.on ? long_pays(s->st, real_bytes) : brick_pays(s->st.lat, s->n, real_bytes);
 }
 
 Engine& engine(sllg_system* s)

@@ -309,6 +309,25 @@ bool brick_pays(const HostLattice& L, int64_t n, size_t real_bytes)
     return real_bytes == 4 ? spins <= 250e3 + 0.75 * (double)n : spins <= 120e3 + 0.93 * (double)n;
 }
 
+bool long_pays(const HostStructure& s, size_t real_bytes)
+{
+    if (!s.far.on)
+        return false;
+    int c[3];
+    long_cells(c);
+    const double tiles = (double)((s.far.nx + c[0] - 1) / c[0]) * ((s.far.ny + c[1] - 1) / c[1]) *
+                         ((s.far.nz + c[2] - 1) / c[2]);
+    double links = 0.0;
+    for (const auto& col : s.columns)
+        links += (double)std::count_if(std::begin(col.type), std::end(col.type), [](int t) { return t >= 0; });
+    const double cols = (double)s.columns.size(), n = (double)s.n;
+    if (real_bytes == 4)
+        return 1.04 * (11.4 + 0.107 * cols + tiles * (13.5e-3 + 18e-6 * cols + 29e-6 * links)) <
+               10.3 + 0.136 * links + n * (18.1e-6 + 0.67e-6 * links);
+    return 1.04 * (10.3 + 0.141 * cols + tiles * (18.0e-3 + 80e-6 * cols + 52e-6 * links)) <
+           11.4 + 0.197 * links + n * (39e-6 + 1.22e-6 * links);
+}
+
 // Link words of the brick step's site classes (see HostStructure): the row
 // of a class is that of its sites (their stencil pattern, or the SELL rows
 // one by one), near links first, each link as the cell offset its class gives

@@ -190,6 +190,22 @@ constexpr int64_t kBrickMaxSites = int64_t(1) << 20;
 //    69.8 and 36.7.  A film of one layer costs about 5/8 of a full brick.
 bool brick_pays(const HostLattice& L, int64_t n, size_t real_bytes);
 
+// Whether the long-range step is faster than the wide two-launch step on a
+// structure that detect_long accepted.  It copies 12 box spins a site and
+// walks the columns whatever the links, the wide form reads every link of
+// every site; and like the bricks its tiles can be partly empty.  The four
+// lines are fits through 15 sets of 12 to 388 links on 729 to 884,736 spins
+// (us per step; within a tenth, on average, of the measurements), the long
+// one raised by a twenty-fifth so that a close call goes to the two-launch
+// step.  Measured, long-range and two-launch, FP32: 12 links 14.6 and 11.6
+// (24^3), 68 and 36 (96^3); 24 links 16.8 and 16.0 (48^3), 45.6 and 31.9
+// (80^3); 56 links 16.9 and 20.4 (48^3), 75 and 67 (96^3); 146 links 17.4 and
+// 33.1 (16^3), 90 and 154 (96^3), 71 and 48 (9 x 9 x 3000); 388 links 27.3 and
+// 72.1 (48^3).  FP64: 12 links 13.0 and 16.7 (16^3), 87 and 67 (96^3); 24
+// links 20.0 and 21.8 (48^3), 91 and 83 (96^3); 146 links 125 and 281 (96^3),
+// 104 and 65 (9 x 9 x 3000).
+bool long_pays(const HostStructure& s, size_t real_bytes);
+
 // Whether the brick step can run on the structure in a precision (bytes per
 // real).  Its tables (set_lattice) exist for a compiled kind with at least kBrickMinEdge cells per periodic axis in which every
 // site of a class lists its links in the same order.

@@ -41,3 +41,41 @@ def test_option_fused_overrides():
     for prec in (sl.FP32, sl.FP64):
         assert _routes("sc", (16, 16, 16), P, prec, 0) == (0, 0)
         assert _routes("sc", (16, 16, 16), P, prec, 2) == (0, 1)
+
+
+def _long_route(dims, keep, prec, fused=1):
+    nx, ny, nz = dims
+    n = nx * ny * nz
+    i = np.arange(n)
+    x, y, z = i % nx, i // nx % ny, i // (nx * ny)
+    offs = [(a, b, c) for c in range(-4, 5) for b in range(-4, 5) for a in range(-4, 5) if (a or b or c) and keep(a, b, c)]
+    col = np.stack([(x + a) % nx + nx * ((y + b) % ny + ny * ((z + c) % nz)) for a, b, c in offs], axis=1)
+    typ = np.tile(np.array([(a * a + b * b + c * c) % 16 for a, b, c in offs], dtype=np.uint8), (n, 1))
+    with sl.SpinSystem(n, precision=prec) as s:
+        s.set_option("check_symmetry", 0)
+        s.set_option("fused", fused)
+        s.set_neighbours(np.arange(n + 1, dtype=np.int64) * len(offs), col.astype(np.int32).ravel(), typ.ravel(),
+                         1e-21 * np.ones(16))
+        s.set_materials(1e-23, 0.0, [0.0, 0.0, 1.0])
+        return s.get_option("brick_active")
+
+
+AXES = lambda *reach: lambda a, b, c: (a == 0) + (b == 0) + (c == 0) == 2 and max(abs(a), abs(b), abs(c)) in reach
+SPHERE = lambda r2: lambda a, b, c: a * a + b * b + c * c <= r2
+
+
+# (cells, links, long-range step in FP32, in FP64)
+LONG = [((16, 16, 16), AXES(1, 4), 0, 1), ((48, 48, 48), AXES(1, 4), 0, 0), ((48, 48, 48), AXES(1, 2, 3, 4), 0, 1),
+        ((80, 80, 80), AXES(1, 2, 3, 4), 0, 0), ((9, 9, 9), SPHERE(5), 1, 1), ((48, 48, 48), SPHERE(5), 1, 1),
+        ((9, 9, 9), SPHERE(20), 1, 1), ((32, 32, 32), SPHERE(20), 1, 1), ((9, 9, 1000), SPHERE(6), 0, 0),
+        ((13, 13, 300), SPHERE(10), 1, 1)]
+
+
+@pytest.mark.parametrize("dims,keep,fp32,fp64", LONG)
+def test_long_range_step_where_it_pays(dims, keep, fp32, fp64):
+    assert (_long_route(dims, keep, sl.FP32), _long_route(dims, keep, sl.FP64)) == (fp32, fp64)
+
+
+def test_option_fused_overrides_long():
+    assert _long_route((9, 9, 9), SPHERE(20), sl.FP32, 0) == 0
+    assert _long_route((9, 9, 9), SPHERE(20), sl.FP32, 2) == 0
