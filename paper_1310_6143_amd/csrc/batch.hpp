@@ -417,8 +417,8 @@ public:
     {
         hip_check(hipSetDevice(device_), "hipSetDevice");
         hip_check(hipMalloc(&d_reps_, sizeof(ReplicaDev<R>) * (size_t)max_replicas), "hipMalloc(reps)");
-        hip_check(hipMalloc(&d_nwork_, sizeof(int)), "hipMalloc(nwork)");
-        hip_check(hipMemset(d_nwork_, 0, sizeof(int)), "hipMemset");
+        hip_check(hipMalloc(&d_nwork_, 2 * sizeof(int)), "hipMalloc(nwork)");
+        hip_check(hipMemset(d_nwork_, 0, 2 * sizeof(int)), "hipMemset");
         host_reps_.resize(max_replicas);
         // pinned staging of the replica table: its per-chunk upload is then a
         // plain DMA on the work stream
@@ -1072,21 +1072,22 @@ public:
         build_bricks(fused);
         // two-launch tiles of the replicas that do not take the brick step
         // (the Monte Carlo records take them in fused mode too)
-        // the reduction items first, so that they run beside the tiles
+        // and behind them their reduction items
         work_.clear();
         auto runs_tiles = [&](const Slot& sl) {
             return sl.used && sl.rec.nsteps > 0 && (fused || !brick_on_ || !sl.b_kind);
         };
         for (size_t q = 0; q < slots_.size(); ++q)
             if (runs_tiles(slots_[q]))
-                for (int32_t g = 0; g * kGroupTiles < slots_[q].rec.blocks; ++g)
-                    work_.push_back(WorkItem{(int32_t)q, -1 - g});
-        for (size_t q = 0; q < slots_.size(); ++q)
-            if (runs_tiles(slots_[q]))
                 for (int32_t b : tile_order(slots_[q].rec.blocks, order_ ? slots_[q].plane_tiles : 0,
                                             group_ > 0 ? group_
                                                        : balanced_group(slots_[q].plane_tiles, slots_[q].rec.tile)))
                     work_.push_back(WorkItem{(int32_t)q, b});
+        const int ntiles = (int)work_.size();
+        for (size_t q = 0; q < slots_.size(); ++q)
+            if (runs_tiles(slots_[q]))
+                for (int32_t g = 0; g * kGroupTiles < slots_[q].rec.blocks; ++g)
+                    work_.push_back(WorkItem{(int32_t)q, -1 - g});
         fwork_.clear();
         if (fused)
             for (size_t q = 0; q < slots_.size(); ++q)
@@ -1150,7 +1151,8 @@ public:
         if (!work_.empty())
             hip_check(hipMemcpy(d_work_, work_.data(), sizeof(WorkItem) * work_.size(), hipMemcpyHostToDevice),
                       "upload work");
-        hip_check(hipMemcpy(d_nwork_, &nwork, sizeof(int), hipMemcpyHostToDevice), "upload nwork");
+        const int counts[2] = {ntiles, nwork - ntiles};
+        hip_check(hipMemcpy(d_nwork_, counts, sizeof(counts), hipMemcpyHostToDevice), "upload nwork");
     }
 
     // Brick lists of the running replicas by kind, uploaded (empty when the
@@ -1384,11 +1386,11 @@ public:
         WorkItem* d_all = nullptr;
         int* d_n = nullptr;
         hip_check(hipMalloc(&d_all, sizeof(WorkItem) * all.size()), "hipMalloc(measure)");
-        hip_check(hipMalloc(&d_n, sizeof(int)), "hipMalloc(measure)");
-        const int n = (int)all.size();
+        hip_check(hipMalloc(&d_n, 2 * sizeof(int)), "hipMalloc(measure)");
+        const int n = (int)all.size(), counts[2] = {n, 0};   // tiles, no reduction items
         hipError_t e = hipMemcpy(d_all, all.data(), sizeof(WorkItem) * all.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipMemcpy(d_n, &n, sizeof(int), hipMemcpyHostToDevice);
+            e = hipMemcpy(d_n, counts, sizeof(counts), hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = launch_predict<R>(d_reps_, d_all, d_n, n, 1, 0, true, variant_, st);
         if (e == hipSuccess)
@@ -1586,7 +1588,7 @@ private:
     std::vector<WorkItem> work_;
     ReplicaDev<R>* d_reps_ = nullptr;
     WorkItem* d_work_ = nullptr;
-    int* d_nwork_ = nullptr;
+    int* d_nwork_ = nullptr;   // tiles and reduction items of d_work_
     int64_t work_cap_ = 0;
     int grid_ = 0;
     int resident_ = 0;

@@ -682,6 +682,24 @@ __device__ __forceinline__ void predict_sites(const ReplicaDev<R>& r, const R* _
     }
 }
 
+// The launch's reduction items, which follow its tiles in the list (n_work:
+// the counts of both): one each to the workgroups that are the first to have
+// no tile under TileIter's mapping (by XCD: the last of each, from XCD 0 on,
+// whose share is the one rounded down), before their tiles where every one
+// has some.  So small systems run them beside the tiles, and the tiles' shares
+// do not shift (listed among the tiles they gave one workgroup of a launch
+// that just fills the chip a second tile: 262,144 FP64 spins 24.2 us a step
+// against 20.0).
+template <typename F>
+__device__ __forceinline__ void for_reductions(const WorkItem* __restrict__ work, const int* __restrict__ n_work,
+                                               int remap, F&& f)
+{
+    const int W = n_work[0], G = n_work[1], grid = (int)gridDim.x, b = (int)blockIdx.x;
+    const int first = remap != 0 && (grid & 7) == 0 ? grid - 8 - (b & ~7) + (b & 7) : grid - 1 - b;
+    for (int q = first; q < G; q += grid)   // uniform over the block
+        f(work[W + q]);
+}
+
 template <typename R, bool MEASURE, int V>
 __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps,
                                           const WorkItem* __restrict__ work,
@@ -690,7 +708,18 @@ __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps
     __shared__ Shared<R> sh;
     __shared__ TileLds<R> tl;
     __shared__ BlockSums red;
-    const int W = *n_work;
+    const int W = n_work[0];
+    // a replica's first reduction item: group partials left by the previous
+    // corrector -> their record
+    for_reductions(work, n_work, remap, [&](const WorkItem& w) {
+        const ReplicaDev<R>& r = reps[w.replica];
+        if (w.block != -1 || !(r.flags & kRecord))
+            return;
+        if (!MEASURE && k >= 2 && k < r.nsteps)
+            final_reduce(r, k - 2, red);
+        else if (MEASURE && k == 0 && r.nsteps >= 2)
+            final_reduce(r, r.nsteps - 2, red);
+    });
     int staged = -1;
     for (TileIter it(W, remap); it.more(); it.next()) {
         const WorkItem w = work[it.t];
@@ -699,17 +728,6 @@ __global__ SLLG_STEP_ATTRS void k_predict(const ReplicaDev<R>* __restrict__ reps
         if (MEASURE ? (!(r.flags & kRecord) || (k == 0 && nsteps <= 0)) : (k >= nsteps))
             continue;   // uniform over the block
         const bool recording = (r.flags & kRecord) != 0;
-        if (w.block < 0) {
-            // the replica's first reduction item: group partials left by the
-            // previous corrector -> their record
-            if (recording && w.block == -1) {
-                if (!MEASURE && k >= 2)
-                    final_reduce(r, k - 2, red);
-                else if (MEASURE && k == 0 && nsteps >= 2)
-                    final_reduce(r, nsteps - 2, red);
-            }
-            continue;
-        }
         const bool partials = recording && (MEASURE || k >= 1);
         const int par = (r.parity + (MEASURE ? (k == 0 ? nsteps : 0) : k)) & 1;
         const R* __restrict__ S = r.S[par];
@@ -799,18 +817,19 @@ __global__ SLLG_STEP_ATTRS void k_correct(const ReplicaDev<R>* __restrict__ reps
     __shared__ Shared<R> sh;
     __shared__ TileLds<R> tl;
     __shared__ BlockSums red;
-    const int W = *n_work;
+    const int W = n_work[0];
+    // reduction item g = -1 - block: that group of the predictor's partials
+    for_reductions(work, n_work, remap, [&](const WorkItem& w) {
+        const ReplicaDev<R>& r = reps[w.replica];
+        if (k >= 1 && k < r.nsteps && (r.flags & kRecord))
+            group_reduce(r, -1 - w.block, red);
+    });
     int staged = -1;
     for (TileIter it(W, remap); it.more(); it.next()) {
         const WorkItem w = work[it.t];
         const ReplicaDev<R>& r = reps[w.replica];
         if (k >= r.nsteps)
             continue;
-        if (w.block < 0) {   // reduction item g = -1 - block: that group of the predictor's partials
-            if ((r.flags & kRecord) && k >= 1)
-                group_reduce(r, -1 - w.block, red);
-            continue;
-        }
         const R* __restrict__ Sp = r.Sp;
         const int T = r.tile;
         const int i0 = w.block * T, wb = i0 - r.halo;

@@ -14,7 +14,8 @@ namespace sllg {
 // measure it only evaluates m and E: of the state after the chunk (k = 0) or
 // of the current state (k = 1).
 // `grid` workgroups are launched; those whose (remapped) index is at or past
-// *n_work (device memory) exit at once, so a captured graph can serve any
+// n_work[0] (device memory: tiles, then the reduction items behind them in the
+// list) exit at once, so a captured graph can serve any
 // batch up to `grid` blocks.
 // variant selects the kernels: 0 uniform materials only, 1 also per-site
 // materials and easy axes, 2 also exchange tensors and cubic anisotropy (the

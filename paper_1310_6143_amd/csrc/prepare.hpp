@@ -177,17 +177,17 @@ constexpr int64_t kBrickMaxSites = int64_t(1) << 20;
 // brick and two-launch, 300 K with records:
 //  - second neighbours: two bricks fill a compute unit's LDS in FP32 and one
 //    does in FP64, so beyond one brick per unit a launch takes half as long
-//    again: FP32 9.0 and 11.9 with 256 bricks (65,536 spins), 13.6 and 12.3
-//    with 405 (93,312), 25.6 and 12.8 with 950 (5 x 5 x 1900 cells); FP64 12.7
-//    and 15.4, 20.2 and 16.1, 37.5 and 17.4.
+//    again: FP32 9.0 and 11.5 with 256 bricks (65,536 spins), 13.6 and 11.9
+//    with 405 (93,312), 25.6 and 12.4 with 950 (5 x 5 x 1900 cells); FP64 12.7
+//    and 14.9, 20.2 and 15.6, 37.5 and 16.9.
 //  - nearest neighbours: the launch's share of a brick, and of the two-launch
 //    step's sites, are lines through the measurements.  FP32: simple cubic
-//    9.7 and 16.1 (64^3), 24.8 and 29.9 (96^3), 33.8 and 32.3 (101^3), 62.7
-//    and 32.8 (5 x 5 x 40000), 67 and 31.5 (1000 x 1000 x 1), 6.9 and 11.0
-//    (256 x 256 x 1); bcc 19.5 and 22.8 (64^3), 36.1 and 33.9 (80^3), 49 and
-//    21.6 (512 x 512 x 1).  FP64: 18.2 and 24.2, 52.4 and 52.8, 63 and 63.7,
-//    137 and 62.6, 137 and 60.5, 10.5 and 14.3; 32.2 and 37.8, 60.5 and 65.8,
-//    69.8 and 36.7.  A film of one layer costs about 5/8 of a full brick.
+//    9.7 and 13.2 (64^3), 24.9 and 29.0 (96^3), 33.8 and 30.9 (101^3), 62.7
+//    and 31.0 (5 x 5 x 40000), 67 and 30.0 (1000 x 1000 x 1), 6.9 and 10.7
+//    (256 x 256 x 1); bcc 19.7 and 20.3 (64^3), 36.1 and 32.3 (80^3), 49 and
+//    19.2 (512 x 512 x 1).  FP64: 18.3 and 19.9, 50.4 and 50.6, 63 and 61.7,
+//    137 and 60.1, 137 and 58.0, 10.6 and 13.7; 32.9 and 34.2, 61.4 and 64.2,
+//    69.8 and 33.0.  A film of one layer costs about 5/8 of a full brick.
 bool brick_pays(const HostLattice& L, int64_t n, size_t real_bytes);
 
 // Whether the long-range step is faster than the wide two-launch step on a
