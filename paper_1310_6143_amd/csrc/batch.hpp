@@ -187,17 +187,21 @@ inline int64_t fused_items(const HostLattice& L, const FusedShape& f)
 // Candidate shapes for a lattice (the autotuner times them; the first is
 // the model's choice, which runs without tuning).  resident(f) gives the
 // workgroups the device (cus compute units) holds at once for shape f.  A
-// compute unit works through ceil(items / cus) items.  FP64: the predictor's
-// noise keeps the vector units busy whatever else is resident, so an item
-// costs its waves (in whole rounds of the four SIMDs) times (planes + 2
-// predictor planes) and a fifth of its corrector planes; the units' whole
-// items decide, not the rounds of the
-// resident workgroups (measured on 90 shapes of bcc blocks of 1.1M to 8.2M
-// spins: within 8% of that law; counting fractions of a round, as before,
-// took 23 x 18 x 32 planes for the 8.2M spins, 438 us a step against 275 of
-// 20 x 20 x 40, and 231 against 157 us for 4.2M).  FP32: every plane costs a
-// round of resident workgroups its barriers and copies (as much as five
-// waves), and each wave its predictor, plane copies and, where it holds
+// compute unit works through ceil(items / cus) items, as many at a time as
+// are resident.  FP64: while the unit holds `busy` waves on its fullest SIMD,
+// a plane takes the latency of its chain (2 of the unit) and the issue of
+// those waves (0.9 each); a fit through 130 shapes each of seven simple-cubic
+// and seven bcc lattices (films of one layer, rods, blocks; 0.9M to 2.1M
+// spins) and the tuner's shapes of 14 blocks of up to 8.2M.  The shape it
+// picks is within 1.1% of the fastest measured one on average, 14% at worst (a
+// simple-cubic slab of 200 x 200 x 50).  The units' whole items decide, not rounds of the resident
+// workgroups (8.2M bcc spins: 23 x 18 x 32 planes 438 us a step, 20 x 20 x 40
+// planes 275); and one 8-wave workgroup a unit is not as good as three of 4
+// waves where registers allow them (simple cubic 1024 x 1024 x 1: 28 x 15
+// cells, 512 threads 105 us, 12 x 16, 256 threads 90; 9 x 9 x 13000: items of
+// 26 planes, two a unit, 85 us, of 17, three a unit, 63).  FP32: every plane
+// costs a round of resident workgroups its barriers and copies (as much as
+// five waves), and each wave its predictor, plane copies and, where it holds
 // tile cells, corrector (4.2M spins 69.7 -> 69.2 us untuned, 1.77M 50.5 ->
 // 43.4, 8.2M 122.7 -> 112.7).  Tiles longer in y than in x run up to a tenth
 // slower in either precision (shorter runs of sites per row copied).
@@ -240,12 +244,12 @@ inline std::vector<FusedShape> fused_candidates(const HostLattice& L, size_t lds
                     const double per_cu = (double)((items + cus - 1) / cus);
                     const double narrow = ty > tx ? 1.08 : 1.0;
                     if (real_bytes == 8) {
-                        // waves per SIMD: a part round counts as a whole
-                        // one, and one wave alone takes 3/4 of what two do
-                        const int simd = (waves + 3) / 4;
-                        const bool lone = simd * std::min<int64_t>(std::max(R / cus, 1), (int64_t)per_cu) == 1;
-                        const double item = 4.0 * simd * (lone ? 1.5 : 1.0) * (planes + 2) + 0.2 * tile_waves * planes;
-                        all.push_back({per_cu * item * narrow, f});
+                        const double conc = std::max(1.0, std::min<double>(R / cus, per_cu));
+                        const double busy = std::ceil(conc * waves / 4.0);
+                        const double item = (0.9 * busy + 2.0) / conc * (planes + 2) + 0.05 * tile_waves * planes;
+                        const double tall = 1.0 + 0.08 * std::min(1.0, std::max(0.0, 2.0 * ty / tx - 2.0));
+                        // rows copied a plane: a shape of fewer, longer ones is a little faster
+                        all.push_back({per_cu * item * tall * (1.0 + 0.003 * py), f});
                         continue;
                     }
                     const double item = waves * ((planes + 2) * 1.0 + (planes + 4) * 0.25) + tile_waves * planes * 0.4;

@@ -309,3 +309,25 @@ def test_records_do_not_change_the_spins(precision):
         Sa, Sb, Sc = a.get_spins(), b.get_spins(), c.get_spins()
     assert np.array_equal(Sa, Sb)
     assert np.array_equal(Sa, Sc)
+
+
+@pytest.mark.parametrize("kind,cells,periodic,threads,planes",
+                         [("sc", (1024, 1024, 1), (1, 1, 0), 256, 1), ("sc", (512, 512, 8), (1, 1, 0), 256, 8),
+                          ("sc", (9, 9, 13000), (1, 1, 1), 256, 17), ("bcc", (64, 64, 128), (1, 1, 1), 512, None)])
+def test_untuned_fp64_shapes(kind, cells, periodic, threads, planes):
+    """The shape that FP64 systems run untuned: simple-cubic films and rods
+    take several 4-wave workgroups a unit, bcc blocks one of 8 waves (their
+    kernel has the registers for no more)."""
+    csr = sl.build_sc(cells, periodic) if kind == "sc" else sl.build_bcc(cells, periodic, True)
+    n = len(csr[0]) - 1
+    with sl.SpinSystem(n, precision=sl.FP64) as s:
+        s.set_option("check_symmetry", 0)
+        s.set_neighbours(csr[0], csr[1], csr[2], [6e-21] if kind == "sc" else [6e-21, 3e-21])
+        s.set_lattice(1 if kind == "sc" else 2, cells, periodic)
+        s.set_materials(1e-23, 0.0, [0.0, 0.0, 1.0])
+        s.set_integrator(0.1, 1.76e11, 1e-16)
+        s.set_spins(np.tile([0.0, 0.0, 1.0], (n, 1)))
+        s.integrate_dev(0)
+        assert s.get_option("fused_active") == 1
+        assert s.get_option("fused_threads") == threads
+        assert planes is None or s.get_option("fused_planes") == planes
