@@ -192,8 +192,9 @@ __device__ __forceinline__ void thermal_normals(uint64_t seed, uint64_t step, ui
 }
 
 __device__ __forceinline__ float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }
-// 1/sqrt(x) for x > 0 (a spin's squared norm after a step, close to 1): the
-// hardware estimate refined by two Newton steps y <- y + (y/2)(1 - x y^2).
+// 1/sqrt(x) for x > 0 and 1/x finite (a spin's squared norm after a step,
+// close to 1, or a squared distance of macrocells): the hardware estimate
+// refined by two Newton steps y <- y + (y/2)(1 - x y^2).
 __device__ __forceinline__ double rsqrt_r(double x)
 {
     double y = __builtin_amdgcn_rsq(x);

@@ -1006,57 +1006,47 @@ __global__ __launch_bounds__(256) void k_demag_moments(const ReplicaDev<R>* __re
 }
 
 constexpr int kDemagBlock = 256;
-// Target cells a thread holds: the sources' LDS reads serve two pairs.
-constexpr int kDemagTargets = 2;
 
 // Partial dipole sums: block (bx, c) takes cells p of block bx and the
 // sources q of chunk c, staged through LDS; dm_part[c] receives the sums.
-// VALU-bound (9 LDS words serve two pairs): 19 instructions a pair, one of
-// them the reciprocal square root; 3 m is staged beside m, and only the
-// tile that holds the block's own cells tests for the self pair.  65,536
-// cells, FP32: 2.17 ms with one target per thread, the factor 3 and the test
-// in every pair (23 instructions), 2.03 ms here.
+// VALU-bound: 19 instructions a pair, one of them the reciprocal square root;
+// 3 m is staged beside m, and only the tile that holds the block's own cells
+// tests for the self pair.  Whole update, with the factor 3 and the test in
+// every pair (23 instructions) and here: FP32 83 and 79 us for 4,096 cells,
+// 566 and 510 for 32,768, 1.98 and 1.78 ms for 64,000; FP64, which also
+// divided 1 by a square root, 110 and 91 us, 1.89 and 1.12 ms, 7.3 and 4.2 ms.
+// Two targets a thread, which share a source's LDS reads, leave half the
+// workgroups: 88 us for 4,096 cells in FP32, 2.02 ms for 64,000, 7.00 instead
+// of 7.05 ms for 125,000.
 template <typename R>
 __global__ __launch_bounds__(kDemagBlock) void k_demag_pairs(const ReplicaDev<R>* __restrict__ rep)
 {
     __shared__ R tile[9][kDemagBlock];
     const ReplicaDev<R>& r = *rep;
     const int nc = r.dm_cells;
-    const int p0 = (int)blockIdx.x * (kDemagBlock * kDemagTargets), t = (int)threadIdx.x;
+    const int p = (int)blockIdx.x * kDemagBlock + (int)threadIdx.x, t = (int)threadIdx.x;
     const int per = (nc + r.dm_chunks - 1) / r.dm_chunks;
     const int qb = (int)blockIdx.y * per, qe = min(nc, qb + per);
-    V3<R> xp[kDemagTargets], h[kDemagTargets];
-#pragma unroll
-    for (int j = 0; j < kDemagTargets; ++j) {
-        const int p = p0 + j * kDemagBlock + t;
-        xp[j] = p < nc ? load3(r.dm_pos, p) : V3<R>{0, 0, 0};
-        h[j] = V3<R>{0, 0, 0};
-    }
-    // sources 0 .. cnt - 1 of the tile on the thread's targets; own: the tile
-    // may hold a target itself
+    const V3<R> xp = p < nc ? load3(r.dm_pos, p) : V3<R>{0, 0, 0};
+    V3<R> h{0, 0, 0};
+    // sources 0 .. cnt - 1 of the tile; own: the tile may hold the target itself
     auto sweep = [&](int q0, int cnt, auto own) {
 #pragma unroll 4
         for (int k = 0; k < cnt; ++k) {
-            const R qx = tile[0][k], qy = tile[1][k], qz = tile[2][k];
-            const R mx = tile[3][k], my = tile[4][k], mz = tile[5][k];
-            const R m3x = tile[6][k], m3y = tile[7][k], m3z = tile[8][k];
-#pragma unroll
-            for (int j = 0; j < kDemagTargets; ++j) {
-                const R dx = qx - xp[j].x, dy = qy - xp[j].y, dz = qz - xp[j].z;
-                R r2 = dx * dx + dy * dy + dz * dz;
-                const bool self = own && q0 + k == p0 + j * kDemagBlock + t;
-                if (own)
-                    r2 = self ? (R)1 : r2;
-                const R inv = rsqrt_r(r2);
-                const R inv2 = inv * inv;
-                R inv3 = inv2 * inv;
-                if (own)
-                    inv3 = self ? (R)0 : inv3;
-                const R md = (m3x * dx + m3y * dy + m3z * dz) * inv2;   // 3 (m . r) / |d| with r = d / |d|
-                h[j].x += (md * dx - mx) * inv3;
-                h[j].y += (md * dy - my) * inv3;
-                h[j].z += (md * dz - mz) * inv3;
-            }
+            const R dx = tile[0][k] - xp.x, dy = tile[1][k] - xp.y, dz = tile[2][k] - xp.z;
+            R r2 = dx * dx + dy * dy + dz * dz;
+            const bool self = own && q0 + k == p;
+            if (own)
+                r2 = self ? (R)1 : r2;
+            const R inv = rsqrt_r(r2);
+            const R inv2 = inv * inv;
+            R inv3 = inv2 * inv;
+            if (own)
+                inv3 = self ? (R)0 : inv3;
+            const R md = (tile[6][k] * dx + tile[7][k] * dy + tile[8][k] * dz) * inv2;   // 3 (m . r) / |d| with r = d / |d|
+            h.x += (md * dx - tile[3][k]) * inv3;
+            h.y += (md * dy - tile[4][k]) * inv3;
+            h.z += (md * dz - tile[5][k]) * inv3;
         }
     };
     for (int q0 = qb; q0 < qe; q0 += kDemagBlock) {
@@ -1075,18 +1065,14 @@ __global__ __launch_bounds__(kDemagBlock) void k_demag_pairs(const ReplicaDev<R>
             tile[8][t] = (R)3 * m.z;
         }
         __syncthreads();
-        const int cnt = min(kDemagBlock, qe - q0);
-        if (q0 + cnt > p0 && q0 < p0 + kDemagBlock * kDemagTargets)
+        const int cnt = min(kDemagBlock, qe - q0), p0 = p - t;
+        if (q0 + cnt > p0 && q0 < p0 + kDemagBlock)
             sweep(q0, cnt, std::true_type{});
         else
             sweep(q0, cnt, std::false_type{});
     }
-#pragma unroll
-    for (int j = 0; j < kDemagTargets; ++j) {
-        const int p = p0 + j * kDemagBlock + t;
-        if (p < nc)
-            store3(r.dm_part + 3 * (int64_t)nc * blockIdx.y, p, h[j]);
-    }
+    if (p < nc)
+        store3(r.dm_part + 3 * (int64_t)nc * blockIdx.y, p, h);
 }
 
 // Chunk sums in chunk order, scaled by mu0 / (4 pi), plus the self term.
@@ -1479,8 +1465,8 @@ hipError_t launch_demag(const ReplicaDev<R>* rep, int cells, int chunks, hipStre
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    constexpr int kPer = kDemagBlock * kDemagTargets;
-    hipLaunchKernelGGL((k_demag_pairs<R>), dim3((cells + kPer - 1) / kPer, chunks), dim3(kDemagBlock), 0, st, rep);
+    hipLaunchKernelGGL((k_demag_pairs<R>), dim3((cells + kDemagBlock - 1) / kDemagBlock, chunks), dim3(kDemagBlock), 0,
+                       st, rep);
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
