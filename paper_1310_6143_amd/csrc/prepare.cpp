@@ -3,6 +3,7 @@
 #include "prepare.hpp"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -338,7 +339,8 @@ static void brick_tables(HostStructure& s)
     s.brick_near = s.brick_far = 0;
     const HostLattice& L = s.lat;
     if (!L.fusable || L.kind == kKindGeneric || s.wide || s.n > kBrickMaxSites || L.nx < kBrickMinEdge ||
-        L.ny < kBrickMinEdge || (L.per[2] && L.nz < kBrickMinEdge))
+        L.ny < kBrickMinEdge || (L.per[2] && L.nz < kBrickMinEdge) ||
+        (!brick_pays(L, s.n, 4) && !brick_pays(L, s.n, 8)))
         return;
     const int classes = 27 * L.nb, pairs = brick_pairs(L.kind);
     const BrickBox box = brick_box(L.kind);
@@ -366,27 +368,70 @@ static void brick_tables(HostStructure& s)
     };
     std::vector<int64_t> site((size_t)classes, -1);   // the class's first site
     std::vector<std::vector<Link>> rows((size_t)classes);
-    std::vector<Link> row;
-    int64_t i = 0;
-    for (int z = 0; z < L.nz; ++z)
-        for (int y = 0; y < L.ny; ++y) {
-            const int czy = edge_class(z, L.nz) * 9 + edge_class(y, L.ny) * 3;
-            for (int x = 0; x < L.nx; ++x)
-                for (int b = 0; b < L.nb; ++b, ++i) {
-                    const size_t c = (size_t)(b * 27 + czy + edge_class(x, L.nx));
-                    if (site[c] < 0) {
-                        site[c] = i;
-                        row_of(i, rows[c]);
-                    } else if (s.stencil) {
-                        if (s.pat_id[(size_t)i] != s.pat_id[(size_t)site[c]])
-                            return;   // the class's rows differ (their order, say)
-                    } else {
-                        row_of(i, row);
-                        if (row != rows[c])
-                            return;
+    auto first_of = [](int cls, int n) { return cls == 0 ? 0 : cls == 2 ? (n > 1 ? n - 1 : -1) : (n > 2 ? 1 : -1); };
+    for (int c = 0; c < classes; ++c) {
+        const int x = first_of(c % 3, L.nx), y = first_of(c / 3 % 3, L.ny), z = first_of(c / 9 % 3, L.nz);
+        if (x < 0 || y < 0 || z < 0)
+            continue;
+        site[(size_t)c] = c / 27 + L.nb * (x + (int64_t)L.nx * (y + (int64_t)L.ny * z));
+        row_of(site[(size_t)c], rows[(size_t)c]);
+    }
+    // every site's row has to be its class's, links and order
+    auto like = [&](int64_t i, int64_t first) {
+        if (s.stencil)
+            return s.pat_id[(size_t)i] == s.pat_id[(size_t)first];
+        if (s.deg[(size_t)i] != s.deg[(size_t)first])
+            return false;
+        const uint32_t* a = &s.nb[(size_t)(s.slice_off[(size_t)(i / kSlice)] + i % kSlice)];
+        const uint32_t* b = &s.nb[(size_t)(s.slice_off[(size_t)(first / kSlice)] + first % kSlice)];
+        const int d = (int)(s.deg[(size_t)i] & 0xFFFFu);
+        for (int k = 0; k < d; ++k)   // type << kColBits plus the offset: no two agree below 2^21 sites
+            if (a[(size_t)k * kSlice] - (uint32_t)i != b[(size_t)k * kSlice] - (uint32_t)first)
+                return false;
+        return true;
+    };
+    std::atomic<bool> alike{true};
+    auto check = [&](int z0, int z1) {
+        for (int z = z0; z < z1 && alike.load(std::memory_order_relaxed); ++z)
+            for (int y = 0; y < L.ny; ++y)
+                for (int b = 0; b < L.nb; ++b) {
+                    const int64_t* cls = &site[(size_t)(b * 27 + edge_class(z, L.nz) * 9 + edge_class(y, L.ny) * 3)];
+                    const int64_t i = b + L.nb * ((int64_t)L.nx * (y + (int64_t)L.ny * z));
+                    bool ok = like(i, cls[0]) && like(i + (int64_t)L.nb * (L.nx - 1), cls[2]);
+                    for (int x = 1; ok && x < L.nx - 1; ++x)
+                        ok = like(i + (int64_t)L.nb * x, cls[1]);
+                    if (!ok) {
+                        alike.store(false, std::memory_order_relaxed);
+                        return;
                     }
                 }
+    };
+    // stencil rows are one byte a site; SELL rows are worth several threads
+    const int n_threads =
+        s.stencil ? 1 : (int)std::min<int64_t>({(int64_t)std::max(1u, std::thread::hardware_concurrency()), 16, L.nz});
+    struct Pool {
+        std::vector<std::thread> all;
+        ~Pool()
+        {
+            for (auto& t : all)
+                t.join();
         }
+    };
+    {
+        Pool pool;
+        int from = 0;   // planes from here on are the caller's
+        try {
+            for (int w = 0; w + 1 < n_threads; ++w) {
+                const int to = (int)((int64_t)L.nz * (w + 1) / n_threads);
+                pool.all.emplace_back(check, from, to);
+                from = to;
+            }
+        } catch (const std::exception&) {   // no more threads
+        }
+        check(from, L.nz);
+    }
+    if (!alike)
+        return;
     std::vector<uint32_t> words((size_t)classes * box.words, 0x00020002u);   // padding: offset 0, code 2
     int most[2] = {0, 0};
     const int dim[3] = {L.nx, L.ny, L.nz};

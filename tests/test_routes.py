@@ -79,3 +79,36 @@ def test_long_range_step_where_it_pays(dims, keep, fp32, fp64):
 def test_option_fused_overrides_long():
     assert _long_route((9, 9, 9), SPHERE(20), sl.FP32, 0) == 0
     assert _long_route((9, 9, 9), SPHERE(20), sl.FP32, 2) == 0
+
+
+@pytest.mark.parametrize("stencil", [1, 0])
+@pytest.mark.parametrize("kind,dims", [("sc", (9, 7, 6)), ("bcc8", (8, 6, 5)), ("bcc14", (8, 6, 7))])
+def test_bricks_need_one_order_of_links_per_class(kind, dims, stencil):
+    """A site that lists its links in another order than the rest of its class
+    (inner, edge or corner cell, first or last plane; either row format) keeps
+    the lattice on the two-launch step."""
+    nb = 1 if kind == "sc" else 2
+    rp, col, typ, _ = sl.build_sc(dims, P) if nb == 1 else sl.build_bcc(dims, P, kind == "bcc14")
+    n = len(rp) - 1
+    rng = np.random.default_rng(3)
+
+    def active(swap):
+        c, t = col.copy(), typ.copy()
+        if swap is not None:
+            a, b = rp[swap], rp[swap + 1] - 1
+            for v in (c, t):
+                v[a], v[b] = v[b], v[a]
+        with sl.SpinSystem(n, precision=sl.FP64) as s:
+            s.set_option("stencil", stencil)
+            s.set_neighbours(rp, c, t, [6e-21, 3e-21] if kind == "bcc14" else [6e-21])
+            s.set_lattice(nb, dims, P)
+            s.set_materials(1e-23, 0.0, [0.0, 0.0, 1.0])
+            return s.get_option("brick_active")
+
+    assert active(None) == 1
+    inner = nb * (2 + dims[0] * (2 + dims[1] * 2))
+    edge = nb * dims[0] * (dims[1] - 2) + nb * (dims[0] - 1)          # last x, first z
+    for site in [inner, inner + nb - 1, edge, n - 1 - nb] + list(rng.integers(nb * 2, n, 4)):
+        x, y, z = site // nb % dims[0], site // (nb * dims[0]) % dims[1], site // (nb * dims[0] * dims[1])
+        alone = all(u in (0, d - 1) for u, d in zip((x, y, z), dims))    # a corner is a class by itself
+        assert active(int(site)) == (1 if alone else 0), (site, x, y, z)
