@@ -281,15 +281,8 @@ inline void item_cells(int kind, int c[3])
         brick_cells(kind, c);
 }
 
-// Bricks or tiles of a lattice.
-inline int64_t brick_items(const HostLattice& L)
-{
-    int c[3];
-    item_cells(L.kind, c);
-    return (int64_t)((L.nx + c[0] - 1) / c[0]) * ((L.ny + c[1] - 1) / c[1]) * ((L.nz + c[2] - 1) / c[2]);
-}
-
-// Bytes of device memory one replica needs (used for admission).
+// Bytes of device memory one replica needs (used for the server's admission,
+// whose requests have no brick or long-range tables).
 inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size_t real_bytes,
                             int64_t rec_cap, int avg_cap)
 {
@@ -321,11 +314,6 @@ inline size_t replica_bytes(const HostStructure& s, const HostMaterials& m, size
             ent += p.size();
         b += r(ent * sizeof(FusedEntry)) + r(s.lat.pats.size() * 16) + r(s.lat.plane_pat.size()) +
              r((size_t)fused_item_cap(s.lat) * 64);
-    } else if (plain_interactions(s, m) && brick_ok(s, real_bytes)) {
-        b += r((size_t)brick_items(s.far.on ? s.far : s.lat) * 64) + r(s.brick_words.size() * 4) +
-             (s.far.on ? r((kLongHead + s.columns.size()) * 4) +
-                             r(s.columns.size() * (2 * kLongReach + 1) * real_bytes)
-                       : 0);
     }
     b += r(m.mat_mu.size() * sizeof(MaterialDev<double>));
     const size_t groups = (blocks + kGroupTiles - 1) / kGroupTiles;
@@ -399,7 +387,6 @@ public:
         std::vector<void*> mem;
         int64_t rec_cap = 0;
         int avg_cap = 0;
-        size_t bytes = 0;
         int plane_tiles = 0;     // see plane_tiles()
         int32_t* d_colour = nullptr;            // Monte Carlo: sites by colour class
         uint16_t* d_colour_pid = nullptr;       // their stencil patterns, in the same order (stencil forms)
@@ -457,10 +444,9 @@ public:
         (void)hipFree(d_reps_);
         (void)hipFree(d_work_);
         (void)hipFree(d_fwork_);
-        for (BrickList& b : brick_) {
-            (void)hipFree(b.items.d);
-            (void)hipFree(b.table);
-        }
+        (void)hipFree(bricks_.d);
+        for (uint32_t* t : brick_tables_)
+            (void)hipFree(t);
         (void)hipFree(d_nwork_);
         (void)hipFree(d_torque_work_);
         (void)hipFree(d_torque_);
@@ -704,7 +690,6 @@ public:
             r.avg_block_len = 1;
             r.avg_blocks = 0;
             set_spins(q, S0);
-            sl.bytes = replica_bytes(s, m, sizeof(R), sl.rec_cap, sl.avg_cap);
             sl.plane_tiles = plane_tiles(s, (int)tile);
             if (!s.colour_sites.empty()) {
                 sl.d_colour = (int32_t*)get(4 * n);
@@ -866,8 +851,8 @@ public:
             mark_dirty();
         }
     }
-    // Brick step: for every replica that can take it, unless the whole
-    // batch runs the fused step.
+    // Brick step: on when every replica of the batch can take it, all with
+    // one kind of lattice, and the fused step does not run.
     void set_brick(bool on)
     {
         if (on != brick_on_) {
@@ -876,8 +861,6 @@ public:
         }
     }
     bool brick_capable(int q) const { return slots_[q].b_kind != 0; }
-    // every running replica takes the brick step
-    bool bricks_only() const { return grid_ == 0 && bricks_ > 0; }
     // Workgroups of the fused kernel the device holds at once for lattice L
     // in shape f: the register limit (queried once per kernel) and the LDS
     // of the compute units.
@@ -1011,7 +994,7 @@ public:
                 host_reps_[q].flags |= kDirect;
             if (!slots_[q].used)
                 host_reps_[q].nsteps = 0;
-            if (takes_brick(slots_[q])) {
+            if (slots_[q].used && brick_kind_) {
                 host_reps_[q].flags |= kBrick;
                 host_reps_[q].f_items = (int32_t)slots_[q].b_items.size() - 1;   // less the record item
             }
@@ -1074,12 +1057,12 @@ public:
             f_plane = std::max(f_plane, fused_plane_bytes(sl.fshape, sl.lat.nb, sizeof(R)));
         }
         build_bricks(fused);
-        // two-launch tiles of the replicas that do not take the brick step
+        // two-launch tiles, unless the brick step runs
         // (the Monte Carlo records take them in fused mode too)
         // and behind them their reduction items
         work_.clear();
         auto runs_tiles = [&](const Slot& sl) {
-            return sl.used && sl.rec.nsteps > 0 && (fused || !brick_on_ || !sl.b_kind);
+            return sl.used && sl.rec.nsteps > 0 && !brick_kind_;
         };
         for (size_t q = 0; q < slots_.size(); ++q)
             if (runs_tiles(slots_[q]))
@@ -1159,60 +1142,66 @@ public:
         hip_check(hipMemcpy(d_nwork_, counts, sizeof(counts), hipMemcpyHostToDevice), "upload nwork");
     }
 
-    // Brick lists of the running replicas by kind, uploaded (empty when the
-    // batch runs the fused step).
+    // Whether the brick step runs (brick_kind_), and its items, uploaded.
     void build_bricks(bool fused)
     {
-        bricks_ = 0;
-        for (int kind = 1; kind < kBrickKinds; ++kind) {
-            BrickList& b = brick_[kind];
-            std::vector<FusedItem> all;
-            if (brick_on_ && !fused)
-                for (const auto& sl : slots_)
-                    if (sl.used && sl.rec.nsteps > 0 && sl.b_kind == kind)
-                        all.insert(all.end(), sl.b_items.begin(), sl.b_items.end());
-            const int n = (int)all.size();
-            if (n > 0 && kind == kKindLong) {
-                b.resident = std::max(long_resident_blocks<R>(device_) & ~7, 8);
-            } else if (n > 0 && !b.table) {
-                const std::vector<uint32_t> tab = brick_table(kind);
-                if (tab.empty())
-                    fail(SLLG_E_STATE, "brick table does not fit its workgroup");
-                uint32_t* d = nullptr;
-                hip_check(hipMalloc(&d, tab.size() * sizeof(uint32_t)), "hipMalloc(brick table)");
-                const hipError_t e = hipMemcpy(d, tab.data(), tab.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
-                if (e != hipSuccess)
-                    (void)hipFree(d);   // b.table stays unset: the next call uploads it again
-                hip_check(e, "upload brick table");
-                b.resident = std::max(brick_resident_blocks<R>(device_, kind) & ~7, 8);
-                b.table = d;
-            }
-            if (n > b.items.cap)
-                drop_graph();
-            b.items.reserve(
-                n,
-                [](size_t bytes) {
-                    void* p = nullptr;
-                    hip_check(hipMalloc(&p, bytes), "hipMalloc(bricks)");
-                    return p;
-                },
-                [](void* p) { (void)hipFree(p); });
-            // as for the tiles: at most the resident workgroups, and always
-            // those for a changing batch (one graph serves it)
-            int grid = std::min((n + 7) & ~7, b.resident);
-            if (round_grid_ && n > 0)
-                grid = b.resident;
-            if (grid != b.grid)
-                drop_graph();
-            b.grid = grid;
-            if (b.items.d) {
-                if (n > 0)
-                    hip_check(hipMemcpy(b.items.d, all.data(), sizeof(FusedItem) * (size_t)n, hipMemcpyHostToDevice),
-                              "upload bricks");
-                hip_check(hipMemcpy(b.items.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
-            }
-            bricks_ += n;
+        int kind = 0;
+        bool bricks = brick_on_ && !fused;
+        for (const auto& sl : slots_) {
+            if (!sl.used || !bricks)
+                continue;
+            bricks = sl.b_kind != 0 && (kind == 0 || kind == sl.b_kind);
+            kind = sl.b_kind;
         }
+        if (!bricks)
+            kind = 0;
+        if (kind != brick_kind_)
+            drop_graph();
+        brick_kind_ = 0;   // until the lists are there
+        brick_grid_ = 0;
+        if (kind == 0)
+            return;
+        std::vector<FusedItem> all;
+        for (const auto& sl : slots_)
+            if (sl.used && sl.rec.nsteps > 0)
+                all.insert(all.end(), sl.b_items.begin(), sl.b_items.end());
+        const int n = (int)all.size();
+        if (kind != kKindLong && !brick_tables_[kind]) {
+            const std::vector<uint32_t> tab = brick_table(kind);
+            if (tab.empty())
+                fail(SLLG_E_STATE, "brick table does not fit its workgroup");
+            uint32_t* d = nullptr;
+            hip_check(hipMalloc(&d, tab.size() * sizeof(uint32_t)), "hipMalloc(brick table)");
+            const hipError_t e = hipMemcpy(d, tab.data(), tab.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+            if (e != hipSuccess)
+                (void)hipFree(d);   // unset: the next call uploads it again
+            hip_check(e, "upload brick table");
+            brick_tables_[kind] = d;
+        }
+        if (n > bricks_.cap || !bricks_.d)
+            drop_graph();
+        bricks_.reserve(
+            std::max(n, 1),
+            [](size_t bytes) {
+                void* p = nullptr;
+                hip_check(hipMalloc(&p, bytes), "hipMalloc(bricks)");
+                return p;
+            },
+            [](void* p) { (void)hipFree(p); });
+        if (n > 0)
+            hip_check(hipMemcpy(bricks_.d, all.data(), sizeof(FusedItem) * (size_t)n, hipMemcpyHostToDevice),
+                      "upload bricks");
+        hip_check(hipMemcpy(bricks_.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
+        // as for the tiles: at most the resident workgroups
+        int& resident = brick_resident_[kind];
+        if (resident == 0)
+            resident = std::max(
+                (kind == kKindLong ? long_resident_blocks<R>(device_) : brick_resident_blocks<R>(device_, kind)) & ~7, 8);
+        const int grid = std::min((n + 7) & ~7, resident);
+        if (grid != graph_brick_grid_)
+            drop_graph();
+        graph_brick_grid_ = brick_grid_ = grid;
+        brick_kind_ = kind;
     }
 
     // Run one chunk of K launch steps; replica q advances mirror(q).nsteps
@@ -1222,7 +1211,7 @@ public:
     {
         sync_tables(st);
         last_stream_ = st;
-        if (grid_ > 0 || bricks_ > 0) {
+        if (grid_ > 0 || brick_grid_ > 0) {
             if (use_graph) {
                 if (!graph_exec_ || graph_K_ != K) {
                     drop_graph();
@@ -1289,9 +1278,10 @@ public:
             hip_check(launch_fused_record<R>(d_reps_, (int)slots_.size(), slot, kFused, st), "record");
             return;
         }
-        if (bricks_ > 0) {
+        if (brick_kind_) {
             hip_check(enqueue_bricks(-1, true, st), "measure");
             hip_check(launch_fused_record<R>(d_reps_, (int)slots_.size(), slot, kBrick, st), "record");
+            return;
         }
         if (grid_ <= 0)
             return;
@@ -1484,22 +1474,20 @@ private:
                 e = launch_fused_finish<R>(d_reps_, nrep, kFused, st);
             return e;
         }
-        for (int k = 0; k < K && e == hipSuccess; ++k) {
-            e = enqueue_bricks(k, false, st);
-            if (e != hipSuccess || grid_ <= 0)
-                continue;
-            e = launch_predict<R>(d_reps_, d_work_, d_nwork_, grid_, k, remap_, false, variant_, st);
-            if (e == hipSuccess)
-                e = launch_correct<R>(d_reps_, d_work_, d_nwork_, grid_, k, remap_, variant_, st);
-        }
-        if (bricks_ > 0) {
+        if (brick_kind_) {
+            for (int k = 0; k < K && e == hipSuccess; ++k)
+                e = enqueue_bricks(k, false, st);
             if (e == hipSuccess)
                 e = enqueue_bricks(0, true, st);
             if (e == hipSuccess)   // records, averaging sums and the advance
                 e = launch_fused_finish<R>(d_reps_, nrep, kBrick, st);
-        }
-        if (grid_ <= 0)
             return e;
+        }
+        for (int k = 0; k < K && e == hipSuccess; ++k) {
+            e = launch_predict<R>(d_reps_, d_work_, d_nwork_, grid_, k, remap_, false, variant_, st);
+            if (e == hipSuccess)
+                e = launch_correct<R>(d_reps_, d_work_, d_nwork_, grid_, k, remap_, variant_, st);
+        }
         if (e == hipSuccess)
             e = launch_predict<R>(d_reps_, d_work_, d_nwork_, grid_, 0, remap_, true, variant_, st);
         if (e == hipSuccess)
@@ -1511,20 +1499,14 @@ private:
         return e;
     }
 
-    // Step k (measure: the m and E sums) of every kind's bricks.
+    // Step k (measure: the m and E sums) of the listed bricks.
     hipError_t enqueue_bricks(int k, bool measure, hipStream_t st)
     {
-        hipError_t e = hipSuccess;
-        for (int kind = 1; kind < kBrickKinds && e == hipSuccess; ++kind) {
-            const BrickList& b = brick_[kind];
-            if (b.grid > 0 && kind == kKindLong)
-                e = launch_long<R>(d_reps_, b.items.d, b.items.count(), b.grid, k, remap_, measure, st);
-            else if (b.grid > 0)
-                e = launch_brick<R>(d_reps_, b.items.d, b.items.count(), b.table, b.grid, k, remap_, measure, kind, st);
-        }
-        return e;
+        if (brick_kind_ == kKindLong)
+            return launch_long<R>(d_reps_, bricks_.d, bricks_.count(), brick_grid_, k, remap_, measure, st);
+        return launch_brick<R>(d_reps_, bricks_.d, bricks_.count(), brick_tables_[brick_kind_], brick_grid_, k, remap_,
+                               measure, brick_kind_, st);
     }
-    bool takes_brick(const Slot& sl) const { return sl.used && brick_on_ && !fused_mode_ && sl.b_kind != 0; }
 
     // Reals from which get_spins takes the staged path, the first time and
     // again (staged_read), and reals per piece.
@@ -1627,17 +1609,15 @@ private:
     FusedItem* d_fwork_ = nullptr;    // items, then their count (int) at fwork_cap_
     int64_t fwork_cap_ = 0;
 
-    // brick step: items and their count per kind, and the kind's site tables
-    static constexpr int kBrickKinds = kKindLong + 1;
-    struct BrickList {
-        ItemList<FusedItem> items;
-        int grid = 0;
-        int resident = 8;
-        uint32_t* table = nullptr;
-    };
-    BrickList brick_[kBrickKinds];
+    // brick step: the kind it runs on (0: it does not), its items, the kinds'
+    // site tables (made at first use) and the launch grid
     bool brick_on_ = false;
-    int64_t bricks_ = 0;              // items listed, all kinds
+    int brick_kind_ = 0;
+    ItemList<FusedItem> bricks_;
+    uint32_t* brick_tables_[kKindLong + 1] = {};
+    int brick_resident_[kKindLong + 1] = {};   // workgroups the device holds (queried once)
+    int brick_grid_ = 0;
+    int graph_brick_grid_ = 0;   // of the captured chunk
 
     bool window_ = true;
     int order_ = 1;

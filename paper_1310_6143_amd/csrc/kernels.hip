@@ -861,8 +861,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_finish(const ReplicaDev<R>* _
 {
     __shared__ BlockSums red;
     const ReplicaDev<R>& r = reps[blockIdx.x];
-    if (!(r.flags & kRecord) || (mode == 0 && (r.nsteps <= 0 || (r.flags & kBrick))))
-        return;   // a brick chunk's records come from its own items
+    if (!(r.flags & kRecord) || (mode == 0 && r.nsteps <= 0))
+        return;
     const int n_groups = (r.blocks + kGroupTiles - 1) / kGroupTiles;
     for (int g = 0; g < n_groups; ++g)
         group_reduce(r, g, red);
@@ -1102,7 +1102,7 @@ template <typename R>
 __global__ void k_advance(ReplicaDev<R>* __restrict__ reps, int n_rep)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n_rep && !(reps[j].flags & kBrick))
+    if (j < n_rep)
         advance_replica(reps[j]);
 }
 
@@ -1322,8 +1322,7 @@ __global__ __launch_bounds__(64) void k_accumulate(const ReplicaDev<R>* __restri
 {
     __shared__ double buf[64][5];
     const ReplicaDev<R>& r = reps[blockIdx.x];
-    if (!(r.flags & kBrick))
-        accumulate_records(r, buf);
+    accumulate_records(r, buf);
 }
 
 }  // namespace
