@@ -78,3 +78,64 @@ def test_long_range_step_matches_oracle(dims, keep, drop, active):
                 g.set_option("fused", 0)
                 assert g.get_option("brick_active") == 0
                 g.integrate(1)
+
+
+def test_new_moments_reach_the_steps_own_couplings():
+    """The step's table holds J / mu_ref: set_materials with another uniform
+    moment on a running system has to rebuild it.  Continued against an oracle
+    that continues with the new moment, and against the two-launch step."""
+    w = _workload((10, 9, 13), _sphere(20))
+    S_ref = w.S0.copy()
+    oracle.System(w).integrate(S_ref, 0, 6)
+    v = _workload((10, 9, 13), _sphere(20))
+    v.mu_s, v.k_u = 0.6 * w.mu_s, 2.0 * w.k_u
+    m_ref, E_ref = oracle.System(v).integrate(S_ref, 6, 9)
+    for prec, bound in ((sl.FP64, 1e-12), (sl.FP32, 2e-5)):
+        for fused in (1, 0):
+            with sl.from_workload(w, precision=prec) as g:
+                g.set_option("fused", fused)
+                g.integrate(6)
+                g.set_materials(v.mu_s[:1], v.k_u[:1], v.easy_axis[:1], per_site=0)
+                assert g.get_option("brick_active") == fused
+                m, E = g.integrate(9)
+                assert max_angle(g.get_spins(), S_ref) < bound
+                assert np.abs(m - m_ref).max() < bound
+                assert (np.abs(E - E_ref) / np.abs(E_ref)).max() < bound
+
+
+@pytest.mark.parametrize("fused", [1, 0])
+@pytest.mark.parametrize("prec", [sl.FP32, sl.FP64])
+def test_non_finite_spins_are_reported(prec, fused):
+    """A field too large for the arithmetic drives the spins to NaN: the step
+    that writes them reports it, at the call's end or at the next call."""
+    w = _workload((9, 9, 9), _sphere(20))
+    w.temperature, w.H = 0.0, np.array([1e300, 0.0, 0.0])
+    with sl.from_workload(w, precision=prec) as g:
+        g.set_option("fused", fused)
+        assert g.get_option("brick_active") == fused
+        g.integrate_dev(3)
+        assert g.get_option("numeric_fault") == 1
+        g.set_spins(w.S0)
+        assert g.get_option("numeric_fault") == 0
+        with pytest.raises(sl.SllgError) as e:
+            g.integrate(2, record=False)
+        assert e.value.name == "SLLG_E_NUMERIC"
+        g.set_spins(w.S0)
+        g.set_conditions(0.0, (0.0, 0.0, 1.0))
+        g.integrate_dev(3)
+        assert g.get_option("numeric_fault") == 0
+
+
+def test_monte_carlo_records_of_the_steps_tiles():
+    """Monte Carlo records take the step's measuring launch: a whole chain
+    with m and E against the oracle."""
+    w = _workload((10, 9, 13), _sphere(20))
+    w.temperature = 900.0
+    S_ref = w.S0.copy()
+    m_ref, E_ref, acc_ref = oracle.System(w).mc(S_ref, 0, 6)
+    for fused in (1, 0):
+        with sl.from_workload(w, precision=sl.FP64) as g:
+            g.set_option("fused", fused)
+            m, E, acc = g.mc(6)
+            assert np.array_equal(acc, acc_ref) and max_angle(g.get_spins(), S_ref) < 1e-12
+            assert np.abs(m - m_ref).max() < 1e-12 and (np.abs(E - E_ref) / np.abs(E_ref)).max() < 1e-12
