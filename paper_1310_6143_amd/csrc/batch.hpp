@@ -1139,7 +1139,10 @@ public:
             hip_check(hipMemcpy(d_work_, work_.data(), sizeof(WorkItem) * work_.size(), hipMemcpyHostToDevice),
                       "upload work");
         const int counts[2] = {ntiles, nwork - ntiles};
-        hip_check(hipMemcpy(d_nwork_, counts, sizeof(counts), hipMemcpyHostToDevice), "upload nwork");
+        if (counts[0] != counts_[0] || counts[1] != counts_[1])
+            hip_check(hipMemcpy(d_nwork_, counts, sizeof(counts), hipMemcpyHostToDevice), "upload nwork");
+        counts_[0] = counts[0];
+        counts_[1] = counts[1];
     }
 
     // Whether the brick step runs (brick_kind_), and its items, uploaded.
@@ -1178,8 +1181,10 @@ public:
             hip_check(e, "upload brick table");
             brick_tables_[kind] = d;
         }
-        if (n > bricks_.cap || !bricks_.d)
+        if (n > bricks_.cap || !bricks_.d) {
             drop_graph();
+            bricks_n_ = -1;
+        }
         bricks_.reserve(
             std::max(n, 1),
             [](size_t bytes) {
@@ -1191,7 +1196,9 @@ public:
         if (n > 0)
             hip_check(hipMemcpy(bricks_.d, all.data(), sizeof(FusedItem) * (size_t)n, hipMemcpyHostToDevice),
                       "upload bricks");
-        hip_check(hipMemcpy(bricks_.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
+        if (n != bricks_n_)   // a copy of its own: only when it changed
+            hip_check(hipMemcpy(bricks_.count(), &n, sizeof(int), hipMemcpyHostToDevice), "upload bricks");
+        bricks_n_ = n;
         // as for the tiles: at most the resident workgroups
         int& resident = brick_resident_[kind];
         if (resident == 0)
@@ -1575,6 +1582,7 @@ private:
     ReplicaDev<R>* d_reps_ = nullptr;
     WorkItem* d_work_ = nullptr;
     int* d_nwork_ = nullptr;   // tiles and reduction items of d_work_
+    int counts_[2] = {0, 0};   // what d_nwork_ holds
     int64_t work_cap_ = 0;
     int grid_ = 0;
     int resident_ = 0;
@@ -1614,6 +1622,7 @@ private:
     bool brick_on_ = false;
     int brick_kind_ = 0;
     ItemList<FusedItem> bricks_;
+    int bricks_n_ = -1;          // the count in device memory (-1: none)
     uint32_t* brick_tables_[kKindLong + 1] = {};
     int brick_resident_[kKindLong + 1] = {};   // workgroups the device holds (queried once)
     int brick_grid_ = 0;
