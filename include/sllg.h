@@ -141,12 +141,13 @@ sllg_status sllg_build_fcc_sphere(double a_nm, double radius_nm, int64_t *n, int
  * uniform materials, scalar exchange, no cubic anisotropy or demagnetising
  * field; in FP64 only lattices whose sites all have the simple-cubic or bcc
  * links (sllg_get_option "lattice" = 2 when the structure qualifies,
- * "fused_active" = 1 when the next integration takes it); smaller lattices
- * of those links run the brick step (one launch per Heun step over bricks of
- * cells, "brick_active" = 1), other systems the two-launch step.  The exchange sum of a site is then added in a fixed
- * order (links into the plane below, its own plane, the plane above), so
- * trajectories agree with the two-launch step to rounding, not bit for
- * bit.  Call after sllg_set_neighbours; a new
+ * "fused_active" = 1 when the next integration takes it).  Its exchange sum
+ * of a site is added in a fixed order (links into the plane below, its own
+ * plane, the plane above), so trajectories agree with the two-launch step to
+ * rounding, not bit for bit.  Smaller lattices of those links run the brick
+ * step (one launch per Heun step over bricks of cells, "brick_active" = 1),
+ * which is the two-launch step's trajectory bit for bit; other systems the
+ * two-launch step.  Call after sllg_set_neighbours; a new
  * neighbour list drops the declaration.  SLLG_E_STATE before
  * sllg_set_neighbours. */
 sllg_status sllg_set_lattice(sllg_system *sys, int n_basis, const int cells[3], const int periodic[3]);

@@ -62,7 +62,7 @@
 // material, 1 per-site materials and easy axes, 2 general (also exchange
 // tensors and cubic anisotropy).  Per-site FP64: 4, so that two 8-wave
 // workgroups share a unit (196,053 ragged spins: 31.1 us a step with 3, when
-// its 383 tiles took two rounds, 25.7 with 4; 24,499 spins 18.4 and 18.8).
+// its 383 tiles took two rounds, 25.1 with 4; 24,499 spins 18.4 and 18.8).
 #define SLLG_STEP_ATTRS                                                                        \
     __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(                       \
         sizeof(R) == 4 ? (V == 0 ? SLLG_WAVES_F32 : V == 1 ? SLLG_WAVES_F32_PS : SLLG_WAVES_F32_GEN)   \
@@ -626,8 +626,8 @@ __device__ __forceinline__ void add_thermal(const MaterialDev<R>& m, const R g[3
 // per-tile partials of m and E for record k - 1; the corrector of the same
 // step sums them by groups, and the next predictor (or the measuring pass at
 // the end of the chunk) adds the groups into the record, each by work items
-// of its own beside the tiles (after a tile of their own these sums were a
-// sixth of a predictor launch on 4,096 spins).  The chunk's last record is
+// of its own (for_reductions; after a tile in the same workgroup these sums
+// were a sixth of a predictor launch on 4,096 spins).  The chunk's last record is
 // completed by k_finish.
 // ---------------------------------------------------------------------------
 // The sites of one tile (PS: per-site materials or axes; otherwise the
