@@ -90,6 +90,22 @@ __device__ __forceinline__ int wrap_cell(int u, int n)
     return m < 0 ? m + n : m;
 }
 
+// m and E terms of one site: S and S.H_ex/2 + (k_u/mu_s)(S.e)^2, with se =
+// S.e as the predictor forms it (-E_i/mu_s is that plus S.H_app, which the
+// record adds from the summed spins).  A replica takes the fused step only
+// with one material, so mu_s is the reference moment and every site weighs
+// 1.  Written with explicit fmas so that the step and the measuring launch
+// round alike.
+template <typename R>
+__device__ __forceinline__ void record_terms(const MaterialDev<R>& m, const V3<R>& s, R se, const V3<R>& hex, R t[4])
+{
+    const R sh = fma(s.z, hex.z, fma(s.y, hex.y, s.x * hex.x));
+    t[0] = s.x;
+    t[1] = s.y;
+    t[2] = s.z;
+    t[3] = fma((R)0.5, sh, m.ku_mu * se * se);
+}
+
 // The terms of one cell (its basis sites added in R, in basis order) into
 // the thread's own FP64 sums, added in plane order: acc[c * AS].  FP32 keeps
 // the sums in LDS (AS = the block size; constant offsets let the four
@@ -306,6 +322,7 @@ __device__ __forceinline__ void plane_step(const ReplicaDev<R>& r, const ItemGeo
     const int z0 = run.z0, z1 = run.z1;
     const R kj[2] = {r.f_kj[0], r.f_kj[1]};
     const V3<R> e{m.axis[0], m.axis[1], m.axis[2]};
+    const V3<R> Happ{r.H[0], r.H[1], r.H[2]};
     const int zp = q - 1;
     const bool zp_exists = zper || (zp >= 0 && zp < nz);
     const bool zp_need = zp >= z0 - 1 && zp <= z1 && zp_exists;
@@ -382,9 +399,16 @@ __device__ __forceinline__ void plane_step(const ReplicaDev<R>& r, const ItemGeo
                 R gn[3] = {0, 0, 0};
                 if (m.sigma != (R)0)
                     thermal_normals(r.seed, run.step, g.col + (uint32_t)b + g.plane_sites * (uint32_t)zw_m1, gn);
-                V3<R> spn;
-                predict_site(r, m, e, s, hex, se, gn, cs.c_th[S1][b], spn, cs.c_base[S1][b]);
+                // thermal plus applied field, held for the corrector
+                const V3<R> tha{fma(m.sigma, gn[0], Happ.x), fma(m.sigma, gn[1], Happ.y),
+                                fma(m.sigma, gn[2], Happ.z)};
+                const R as = m.ani * se;
+                const V3<R> h{fma(as, e.x, hex.x) + tha.x, fma(as, e.y, hex.y) + tha.y, fma(as, e.z, hex.z) + tha.z};
+                const V3<R> ds = llg_step(s, h, r.gdt, r.alpha);
+                const V3<R> spn = normalised(V3<R>{s.x + ds.x, s.y + ds.y, s.z + ds.z});
+                cs.c_th[S1][b] = tha;
                 cs.c_sp[S1][b] = spn;
+                cs.c_base[S1][b] = V3<R>{s.x + (R)0.5 * ds.x, s.y + (R)0.5 * ds.y, s.z + (R)0.5 * ds.z};
                 slot_store<R, ZOFF>(sp + g.own(b), spn);
             }
         }
@@ -425,7 +449,15 @@ __device__ __forceinline__ void plane_step(const ReplicaDev<R>& r, const ItemGeo
         for (int b = 0; b < NB; ++b) {
             // E: corrector of plane q - 2
             if (zc_own) {
-                const V3<R> sn = correct_site(r, m, e, cs.c_sp[S0][b], cs.hc[S0][b], cs.c_th[S0][b], cs.c_base[S0][b]);
+                const V3<R> s = cs.c_sp[S0][b];
+                const R as = m.ani * dot(s, e);
+                const V3<R> h{fma(as, e.x, cs.hc[S0][b].x) + cs.c_th[S0][b].x,
+                              fma(as, e.y, cs.hc[S0][b].y) + cs.c_th[S0][b].y,
+                              fma(as, e.z, cs.hc[S0][b].z) + cs.c_th[S0][b].z};
+                // half the step's dS' dt (a step of dt / 2: the halving is exact)
+                const V3<R> dsh = llg_step(s, h, (R)0.5 * r.gdt, r.alpha);
+                const V3<R> sn = normalised(V3<R>{cs.c_base[S0][b].x + dsh.x, cs.c_base[S0][b].y + dsh.y,
+                                                  cs.c_base[S0][b].z + dsh.z});
                 // ordinary stores: the L2 merges the lanes' 12- or 24-byte
                 // spins into whole lines (streaming stores of FP64 spins
                 // reached memory as 1.4 times their bytes, for no gain in time)
@@ -651,7 +683,10 @@ __device__ __forceinline__ void fused_item(const ReplicaDev<R>& r, const FusedIt
 // pattern tables.
 // Registers capped for four waves per SIMD in FP32 (two 512-lane or four
 // 256-lane workgroups per compute unit), two in FP64 (twice the registers
-// per column).
+// per column).  Simple cubic in FP32 below 1024 lanes: six waves; the step
+// with records would take 81 to 83 registers, and capped at 80 (three of
+// them spilled) a third workgroup of 512 lanes fits (22 x 19 cells on 1024 x
+// 1024 x 1 spins 47.2 -> 39.7 us, 22 x 16 x 8 on 128^3 43.1 -> 36.3).
 #ifndef SLLG_FUSED_WAVES
 #define SLLG_FUSED_WAVES 4
 #endif
@@ -660,7 +695,7 @@ __device__ __forceinline__ void fused_item(const ReplicaDev<R>& r, const FusedIt
 #endif
 
 template <typename R, int KIND, int NB, int BT, bool MEASURE, bool REC>
-__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? SLLG_FUSED_WAVES
+__global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? (KIND == kKindSc6 && BT < 1024 ? 6 : SLLG_FUSED_WAVES)
                                                                                    : SLLG_FUSED_WAVES_F64))) void k_fused(const ReplicaDev<R>* __restrict__ reps,
                                               const FusedItem* __restrict__ items,
                                               const int* __restrict__ n_items, int k, int remap, int plane_bytes)
